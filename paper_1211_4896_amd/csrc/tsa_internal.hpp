@@ -71,6 +71,25 @@ int region_box(const tsa_cube* c, const tsa_region* r, tsa_region* b);
 int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom* g, bool* vec, int64_t* volume);
 size_t single_ws_bytes(int64_t volume);
 
+// int16 regions answered from the counts of their values (tsa_count16.hip):
+// what one call asks of them.
+struct Count16Ask {
+  tsa_result* out;  // moments and median fields (may be null)
+  double* qout;     // quantile: (value, width, count); MAD: (median, MAD, count)
+  uint64_t* counts; // histogram over [min, max] (null: none) and outliers (may be null)
+  uint64_t* outl;
+  int32_t nbins;
+  int32_t moments, rank;  // rank 1: lower median, 2: quantile q
+  int32_t digits, mad, write_counts;
+  double q;
+};
+size_t count16_scratch_bytes();
+size_t count16_small_bytes();
+int count16_grid(int64_t volume, int blocks);
+int count16_mode(int64_t volume, int grid, size_t table_bytes, const Count16Ask& ask);
+int run_count16(const Geom& g, bool vec, int grid, int mode, void* scratch, void* small, void* tables,
+                const Count16Ask& ask, hipStream_t s);
+
 int run_moments(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out, void* d_ws, size_t ws_bytes,
                 tsa_stream_t stream);
 int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, float hi, int32_t nbins,

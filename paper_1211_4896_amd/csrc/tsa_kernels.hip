@@ -1111,6 +1111,17 @@ static int prepare(const tsa_cube* cube, const tsa_region* region, void* d_ws, s
   return TSA_OK;
 }
 
+// int16 regions large enough for it are answered from one count of their
+// values; returns false when the call takes the passes by key digits.
+static bool try_count16(const tsa_cube* cube, const Prep& P, const Count16Ask& ask, int* st) {
+  if (cube->dtype != TSA_I16) return false;
+  const int grid = count16_grid(P.volume, pass_grid(P.g, P.vec, 1024, P.dev.cus));
+  const int mode = count16_mode(P.volume, grid, 4 * (size_t)P.L.cand_cap, ask);
+  if (!mode) return false;
+  *st = run_count16(P.g, P.vec, grid, mode, P.ws + P.L.hcopy, P.ws + P.L.partials, P.ws + P.L.cand, ask, P.s);
+  return true;
+}
+
 static uint32_t rep_shift_for(int nbins, size_t lds_budget) {
   const Tuning& T = tuning();
   uint32_t r = 0;
@@ -1269,6 +1280,11 @@ int run_median(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out
   Prep P;
   int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcSelect);
   if (st) return st;
+  Count16Ask ask{};
+  ask.out = d_out;
+  ask.rank = 1;
+  ask.write_counts = 1;
+  if (try_count16(cube, P, ask, &st)) return st;
   reset_select(P);
   SelState* stp = (SelState*)(P.ws + P.L.state);
   uint64_t* h1 = (uint64_t*)(P.ws + P.L.hist1);
@@ -1526,6 +1542,14 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
   const size_t lds16 = ((((size_t)nbins + 1) / 2) + kBins2) * 4;
   if (wide && lds16 + 10240 > P.dev.lds_per_block) return TSA_ENOTSUP;
   uint64_t* outl = d_outliers ? d_outliers : (uint64_t*)(P.ws + P.L.outl);
+  Count16Ask ask{};
+  ask.out = d_out;
+  ask.counts = d_counts;
+  ask.outl = outl;
+  ask.nbins = nbins;
+  ask.moments = 1;
+  ask.rank = 1;
+  if (try_count16(cube, P, ask, &st)) return st;
   reset_select(P, d_counts, nbins, outl);
   Partial* parts = (Partial*)(P.ws + P.L.partials);
   SelState* stp = (SelState*)(P.ws + P.L.state);
@@ -1616,6 +1640,12 @@ int run_quantile(const tsa_cube* cube, const tsa_region* region, double q, int32
   Prep P;
   int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcSelect);
   if (st) return st;
+  Count16Ask ask{};
+  ask.qout = d_out;
+  ask.rank = 2;
+  ask.q = q;
+  ask.digits = digits;
+  if (try_count16(cube, P, ask, &st)) return st;
   reset_select(P);
   SelState* stp = (SelState*)(P.ws + P.L.state);
   tsa_result* scratch = (tsa_result*)(P.ws + P.L.result);
@@ -1644,6 +1674,11 @@ int run_mad(const tsa_cube* cube, const tsa_region* region, double* d_out, void*
   Prep P;
   int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcSelect);
   if (st) return st;
+  Count16Ask ask{};
+  ask.qout = d_out;
+  ask.rank = 1;
+  ask.mad = 1;
+  if (try_count16(cube, P, ask, &st)) return st;
   reset_select(P);
   SelState* med = (SelState*)(P.ws + P.L.state);
   SelState* sb = (SelState*)(P.ws + P.L.state2);

@@ -232,4 +232,49 @@ TSA_DEV void walk(const Geom& g, F& f) {
   }
 }
 
+// walk() for accumulators that take a whole vector at once (f.vec(uint4)):
+// the contiguous geometry's full chunks go through it, the next chunk's loads
+// issued before the present one is consumed, so the wave's processing never
+// leaves it without loads in flight.  Everything else (the last chunk, the
+// elements outside the vectors, rows) is walk()'s.
+template <int DT, bool VEC, int U, bool NT, class F>
+TSA_DEV void walk_stream(const Geom& g, F& f) {
+  if constexpr (!VEC) {
+    walk<DT, VEC, U, NT>(g, f);
+  } else {
+    if (g.mode != 0) {
+      walk<DT, VEC, U, NT>(g, f);
+      return;
+    }
+    const uint4* vb = (const uint4*)g.base;
+    const int64_t bs = blockDim.x, chunk = bs * U, stride = chunk * gridDim.x;
+    int64_t cb = g.v0 + (int64_t)blockIdx.x * chunk;
+    if (cb + chunk <= g.v1) {
+      uint4 r[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) r[u] = load16<NT>(vb + cb + threadIdx.x + u * bs);
+      for (;;) {
+        cb += stride;
+        const bool more = cb + chunk <= g.v1;  // the same for the whole block
+        uint4 n[U];
+        if (more) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) n[u] = load16<NT>(vb + cb + threadIdx.x + u * bs);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) f.vec(r[u]);
+        f.chunk();
+        if (!more) break;
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = n[u];
+      }
+    }
+    // this block's share of what is left: the last, partial chunk, and the
+    // elements before the first and after the last vector (block 0)
+    Geom rest = g;
+    rest.v0 = cb - (int64_t)blockIdx.x * chunk;  // walk() starts block b at v0 + b * chunk
+    walk<DT, VEC, U, NT>(rest, f);
+  }
+}
+
 }  // namespace tsa
