@@ -13,6 +13,9 @@
 //    every row carry the same element masks.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "tsa_device.hpp"
 
 namespace tsa {
@@ -232,10 +235,25 @@ TSA_DEV void walk(const Geom& g, F& f) {
   }
 }
 
-// walk() for accumulators that take a whole vector at once (f.vec(uint4)):
-// the contiguous geometry's full chunks go through it, the next chunk's loads
-// issued before the present one is consumed, so the wave's processing never
-// leaves it without loads in flight.  Everything else (the last chunk, the
+// One whole vector: f.vec(uint4) where the accumulator has it, else its elements.
+template <class F, class = void>
+struct TakesVec : std::false_type {};
+template <class F>
+struct TakesVec<F, std::void_t<decltype(std::declval<F&>().vec(uint4{}))>> : std::true_type {};
+template <int DT, class F>
+TSA_DEV void visit_vec(const uint4& r, F& f) {
+  if constexpr (TakesVec<F>::value) {
+    f.vec(r);
+  } else {
+#pragma unroll
+    for (int e = 0; e < Ty<DT>::EPV; ++e) f(Ty<DT>::get(r, e), true);
+  }
+}
+
+// walk() with the loads a step ahead: in the contiguous geometry's full
+// chunks the next chunk's loads are issued before the present one is
+// consumed, so a wave's processing never leaves it without loads in flight
+// (U more vectors of registers).  Everything else (the last chunk, the
 // elements outside the vectors, rows) is walk()'s.
 template <int DT, bool VEC, int U, bool NT, class F>
 TSA_DEV void walk_stream(const Geom& g, F& f) {
@@ -262,7 +280,7 @@ TSA_DEV void walk_stream(const Geom& g, F& f) {
           for (int u = 0; u < U; ++u) n[u] = load16<NT>(vb + cb + threadIdx.x + u * bs);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) f.vec(r[u]);
+        for (int u = 0; u < U; ++u) visit_vec<DT>(r[u], f);
         f.chunk();
         if (!more) break;
 #pragma unroll
