@@ -313,16 +313,6 @@ TSA_DEV bool block_wait_ge(const uint32_t* p, uint32_t v, uint32_t* err, BShared
   return ok;
 }
 
-// Every wave waits until its own global stores and atomics are acknowledged
-// (s_waitcnt vmcnt(0)) before the barrier after which one thread publishes
-// the block's work with an agent-scope release: a workgroup barrier alone
-// does not wait for other waves' writes to reach the L2 that the release
-// writes back.
-TSA_DEV void block_writes_done() {
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt 0; expcnt and lgkmcnt not waited for
-  __syncthreads();
-}
-
 // ---------------------------------------------------------------------------
 // epilogues (whole block)
 // ---------------------------------------------------------------------------

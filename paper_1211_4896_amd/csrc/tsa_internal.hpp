@@ -17,7 +17,7 @@ namespace tsa {
 
 constexpr int kUnroll = 4;            // 16-byte loads in flight per lane
 constexpr uint32_t kTileUnits = 8192; // vectors per rows tile (single-region calls)
-constexpr int kMaxBlocks = 8192;      // upper bound of a pass grid (moment partial slots)
+constexpr int kMaxBlocks = 7936;      // upper bound of a pass grid (moment partial slots)
 // The fused passes add their per-block counts into kHistCopies copies of a
 // histogram (block b into copy b % kHistCopies), summed by the next one-block
 // kernel: a thousand blocks ending together otherwise queue on the same

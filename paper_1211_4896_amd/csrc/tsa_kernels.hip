@@ -12,11 +12,6 @@ namespace tsa {
 // ---------------------------------------------------------------------------
 // small utility kernels
 // ---------------------------------------------------------------------------
-__global__ void k_fill32(uint32_t* __restrict__ p, uint64_t n, uint32_t v) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
 // Several disjoint ranges filled by one launch: on a small cube the gaps
 // between dependent launches, not the bytes, set the time of the clears.
 struct FillRange {
@@ -25,11 +20,16 @@ struct FillRange {
   uint32_t v, pad;
 };
 constexpr int kMaxFills = 6;
+// The selection states of a call are set in the same launch (st: where, null
+// for none).
 struct FillSet {
   FillRange r[kMaxFills];
   int count, pad;
+  SelState* st[2];
+  SelState init[2];
 };
 __global__ void k_fill_set(FillSet f) {
+  if (blockIdx.x == 0 && threadIdx.x < 2 && f.st[threadIdx.x]) *f.st[threadIdx.x] = f.init[threadIdx.x];
   const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
   for (int k = 0; k < f.count; ++k)
     for (uint64_t i = i0; i < f.r[k].n; i += stride) f.r[k].p[i] = f.r[k].v;
@@ -150,10 +150,155 @@ __global__ __launch_bounds__(1024) void k_hist_win(Geom g, float lo, float hi, f
 }
 
 // ---------------------------------------------------------------------------
+// digit selection (one block)
+// ---------------------------------------------------------------------------
+TSA_DEV double value_of_key(uint32_t k, int dtype) {
+  return dtype == 0 ? (double)__uint_as_float(f32bits_of_key(k)) : (double)i16_of_key(k);
+}
+
+struct SelectShared {
+  uint64_t wsum[16];
+  uint32_t found;
+};
+
+// Whole block: choose the digit of the current level from its histogram.
+// Level 1 also fixes n and the rank k = floor((n-1)/2) of the lower median.
+// When the key is complete, writes the median (and, if write_counts, the
+// count fields) to *out.
+// With qout != NULL the finished selection goes to qout[0..2] = (value, width of
+// the bucket it came from (0 when all digits were selected), count) instead of
+// out->median.  st->rank_mode / q / levels select the rank and an early stop.
+TSA_DEV void select_level(int level, const uint64_t* __restrict__ hist, SelState* st, int dtype, uint64_t volume,
+                          tsa_result* out, bool write_counts, SelectShared& sm, double* qout = nullptr) {
+  if (st->done) return;
+  const int nb = level == 3 ? kBins3 : kBins1;
+  const int shift = level == 1 ? kShift1 : level == 2 ? kShift2 : 0;
+  const int t = threadIdx.x, bs = blockDim.x;
+  const int per = (nb + bs - 1) / bs;  // at most 16: blocks have 256 threads or more
+  const int b0 = t * per;
+  uint64_t h[16], local = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) h[i] = (i < per && b0 + i < nb) ? hist[b0 + i] : 0;  // all in flight at once
+#pragma unroll
+  for (int i = 0; i < 16; ++i) local += h[i];
+  // block exclusive scan of `local`
+  const int lane = t % kWave, w = t / kWave;
+  uint64_t inc = local;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint64_t y = __shfl_up(inc, o);
+    if (lane >= o) inc += y;
+  }
+  if (lane == kWave - 1) sm.wsum[w] = inc;
+  if (t == 0) sm.found = 0;
+  __syncthreads();
+  uint64_t base = inc - local, total = 0;
+  for (int i = 0; i < bs / kWave; ++i) {
+    if (i < w) base += sm.wsum[i];
+    total += sm.wsum[i];
+  }
+  uint64_t n = level == 1 ? total : st->n;
+  if (level == 1 && n == 0) {
+    __syncthreads();
+    if (t == 0) {
+      st->n = 0;
+      st->done = 1;
+      if (qout) {
+        qout[0] = qout[1] = __builtin_nan("");
+        qout[2] = 0.0;
+      }
+      out->median = __builtin_nan("");
+      if (write_counts) {
+        out->count = 0;
+        out->nan_count = volume;
+        out->status = TSA_OK;
+      }
+    }
+    return;
+  }
+  uint64_t k = st->k;
+  if (level == 1) {
+    if (st->rank_mode) {
+      const double kk = floor(st->q * (double)(n - 1));
+      k = kk <= 0.0 ? 0 : kk >= (double)(n - 1) ? n - 1 : (uint64_t)kk;
+    } else {
+      k = (n - 1) / 2;
+    }
+  }
+  __syncthreads();  // every thread has read st before it changes
+  if (local > 0 && k >= base && k < base + local) {
+    uint64_t cum = base, bucket = 0, below = base;
+    int d = b0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {  // the last bin that starts at or below k and is not empty
+      if (h[i] && k >= below) {
+        d = b0 + i;
+        cum = below;
+        bucket = h[i];
+      }
+      below += h[i];
+    }
+    const uint32_t prefix = (level == 1 ? 0u : st->prefix) | ((uint32_t)d << shift);
+    st->n = n;
+    st->k = k - cum;
+    st->bucket_n = bucket;
+    st->prefix = prefix;
+    st->level = level;
+    if (level == 1) st->compact = bucket <= st->cand_cap ? 1u : 0u;
+    const bool exact = level == 3 || (dtype == 1 && level == 2);
+    const bool complete = exact || (st->levels >= 1 && (uint32_t)level >= st->levels);
+    if (complete) {
+      st->done = 1;
+      st->result_key = prefix;
+      if (qout) {
+        // the bucket [prefix, prefix | rest] holds the rank: its smallest value
+        // and its width bound the early answer
+        uint32_t rest = level == 1 ? 0x000FFFFFu : level == 2 ? 0xFFu : 0u;
+        if (dtype == 1) rest &= 0xFFFF0000u;
+        double lo = value_of_key(prefix, dtype), hi = value_of_key(prefix | rest, dtype);
+        if (lo != lo) lo = -__builtin_inf();
+        if (hi != hi) hi = __builtin_inf();
+        qout[0] = lo;
+        qout[1] = exact ? 0.0 : hi - lo;
+        qout[2] = (double)n;
+      }
+      out->median = value_of_key(prefix, dtype);
+      if (write_counts) {
+        out->count = n;
+        out->nan_count = volume - n;
+        out->status = TSA_OK;
+      }
+    }
+    sm.found = 1;
+  }
+  __syncthreads();
+  if (t == 0 && !sm.found) {  // inconsistent histogram: never expected
+    st->done = 1;
+    out->median = __builtin_nan("");
+    out->status = TSA_EDEVICE;
+  }
+}
+
+// What the last block of a digit pass needs to choose the digit.
+struct Tail {
+  tsa_result* out;
+  double* qout;
+  uint64_t volume;
+  Arrive* arrive;  // by digit; null: the pass goes out in several launches, the digit is chosen by k_select
+  int32_t dtype, write_counts;
+};
+TSA_DEV void select_tail(int level, const uint64_t* hist, SelState* st, const Tail& tl) {
+  __shared__ SelectShared sm;
+  if (!tl.arrive || !last_block(tl.arrive + (level - 1))) return;
+  select_level(level, hist, st, tl.dtype, tl.volume, tl.out, tl.write_counts != 0, sm, tl.qout);
+}
+
+// ---------------------------------------------------------------------------
 // radix selection: level passes over the cube
 // ---------------------------------------------------------------------------
 template <int DT, bool VEC, bool NT>
-__global__ __launch_bounds__(1024) void k_level1(Geom g, uint32_t rshift, uint64_t* __restrict__ hist1) {
+__global__ __launch_bounds__(1024) void k_level1(Geom g, uint32_t rshift, SelState* __restrict__ st,
+                                                 uint64_t* __restrict__ hist1, Tail tl) {
   extern __shared__ uint32_t lds[];
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
@@ -161,11 +306,12 @@ __global__ __launch_bounds__(1024) void k_level1(Geom g, uint32_t rshift, uint64
   walk<DT, VEC, kUnroll, NT>(g, d);
   __syncthreads();
   lds_flush(lds, kBins1, rshift, hist1);
+  select_tail(1, hist1, st, tl);
 }
 
 template <int DT, bool VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_level2(Geom g, SelState* __restrict__ st, uint64_t* __restrict__ hist2,
-                                                 uint32_t* __restrict__ cand) {
+                                                 uint32_t* __restrict__ cand, Tail tl) {
   __shared__ uint32_t lds[kBins2];
   __shared__ CandShared cs;
   if (st->done) return;
@@ -176,15 +322,31 @@ __global__ __launch_bounds__(1024) void k_level2(Geom g, SelState* __restrict__ 
   a.finish();
   __syncthreads();
   lds_flush(lds, kBins2, 0, hist2);
+  select_tail(2, hist2, st, tl);
 }
 
 // Level 3 reads the candidate list when level 2 made one, else the cube.
 // first = 0: one more slab of a scan cut into slabs (the candidates, when
-// there are any, were counted with the first).
+// there are any, were counted with the first).  hc: pass B's histogram copies
+// to add up (none for a selection alone); the launch's blocks share the bins.
+struct HistCopies {
+  const uint64_t* copies;
+  uint64_t* counts;
+  int32_t nbins;
+};
 template <int DT, bool VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_level3(Geom g, SelState* __restrict__ st, uint64_t* __restrict__ hist3,
-                                                 const uint32_t* __restrict__ cand, int first) {
+                                                 const uint32_t* __restrict__ cand, int first, Tail tl,
+                                                 HistCopies hc) {
   __shared__ uint32_t lds[kBins3];
+  if (hc.copies) {
+    for (uint32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < (uint32_t)hc.nbins; b += gridDim.x * blockDim.x) {
+      uint64_t c = 0;
+#pragma unroll
+      for (int k = 0; k < kHistCopies; ++k) c += hc.copies[(size_t)k * (uint32_t)hc.nbins + b];
+      hc.counts[b] = c;
+    }
+  }
   if (st->done || (st->compact && !first)) return;
   lds_zero(lds, kBins3);
   __syncthreads();
@@ -201,21 +363,23 @@ __global__ __launch_bounds__(1024) void k_level3(Geom g, SelState* __restrict__ 
   }
   __syncthreads();
   lds_flush(lds, kBins3, 0, hist3);
+  select_tail(3, hist3, st, tl);
 }
 
 // ---------------------------------------------------------------------------
 // one-block epilogues: moments merge and digit selection
 // ---------------------------------------------------------------------------
 
-TSA_DEV double value_of_key(uint32_t k, int dtype) {
-  return dtype == 0 ? (double)__uint_as_float(f32bits_of_key(k)) : (double)i16_of_key(k);
-}
-
-struct MergeShared {
-  double n[1024], m[1024], q[1024];
-  uint32_t kmin[1024], kmax[1024];
-  int first;
+// Per-thread arrays of a block's merge (32 bytes a thread).
+struct MergeScratch {
+  double *n, *m, *q;
+  uint32_t *kmin, *kmax;
 };
+TSA_DEV MergeScratch merge_scratch(double* d) {
+  const uint32_t bs = blockDim.x;
+  uint32_t* u = (uint32_t*)(d + 3 * bs);
+  return MergeScratch{d, d + bs, d + 2 * bs, u, u + bs};
+}
 
 // Whole block: merge np partials in a fixed order (each thread a strided
 // sequence, then a pairwise tree) and write the moments fields of *out.
@@ -224,22 +388,23 @@ struct MergeShared {
 // lanes); they are merged about one reference, the ref of the first partial
 // with a finite mean, which the mean gets back at the end.
 TSA_DEV void merge_moments(const Partial* __restrict__ parts, int np, int dtype, uint64_t volume, tsa_result* out,
-                           MergeShared& sm, uint64_t& n_out, uint32_t& kmin_out, uint32_t& kmax_out,
+                           const MergeScratch& sm, uint64_t& n_out, uint32_t& kmin_out, uint32_t& kmax_out,
                            bool centered = false) {
+  __shared__ int first;
   const int t = threadIdx.x, bs = blockDim.x;
   double ref0 = 0.0;
   if (centered) {
-    if (t == 0) sm.first = np;
+    if (t == 0) first = np;
     __syncthreads();
     for (int i = t; i < np; i += bs) {
       const Partial& p = parts[i];
       if (p.n && __builtin_isfinite(p.s)) {
-        atomicMin(&sm.first, i);
+        atomicMin(&first, i);
         break;
       }
     }
     __syncthreads();
-    if (sm.first < np) ref0 = parts[sm.first].ref;
+    if (first < np) ref0 = parts[first].ref;
   }
   double n = 0.0, m = 0.0, q = 0.0;
   uint32_t mn = 0xFFFFFFFFu, mx = 0u;
@@ -303,131 +468,10 @@ TSA_DEV void merge_moments(const Partial* __restrict__ parts, int np, int dtype,
 
 __global__ __launch_bounds__(1024) void k_moments_merge(const Partial* __restrict__ parts, int np, int dtype,
                                                         uint64_t volume, tsa_result* out) {
-  __shared__ MergeShared sm;
+  __shared__ double sm[4 * 1024];
   uint64_t n;
   uint32_t a, b;
-  merge_moments(parts, np, dtype, volume, out, sm, n, a, b, dtype == 0);
-}
-
-struct SelectShared {
-  uint64_t wsum[16];
-  uint32_t found;
-};
-
-// Whole block: choose the digit of the current level from its histogram.
-// Level 1 also fixes n and the rank k = floor((n-1)/2) of the lower median.
-// When the key is complete, writes the median (and, if write_counts, the
-// count fields) to *out.
-// With qout != NULL the finished selection goes to qout[0..2] = (value, width of
-// the bucket it came from (0 when all digits were selected), count) instead of
-// out->median.  st->rank_mode / q / levels select the rank and an early stop.
-TSA_DEV void select_level(int level, const uint64_t* __restrict__ hist, SelState* st, int dtype, uint64_t volume,
-                          tsa_result* out, bool write_counts, SelectShared& sm, double* qout = nullptr) {
-  if (st->done) return;
-  const int nb = level == 3 ? kBins3 : kBins1;
-  const int shift = level == 1 ? kShift1 : level == 2 ? kShift2 : 0;
-  const int t = threadIdx.x, bs = blockDim.x;
-  const int per = (nb + bs - 1) / bs;
-  const int b0 = t * per;
-  uint64_t local = 0;
-  for (int i = 0; i < per; ++i)
-    if (b0 + i < nb) local += hist[b0 + i];
-  // block exclusive scan of `local`
-  const int lane = t % kWave, w = t / kWave;
-  uint64_t inc = local;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint64_t y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
-  }
-  if (lane == kWave - 1) sm.wsum[w] = inc;
-  if (t == 0) sm.found = 0;
-  __syncthreads();
-  uint64_t base = inc - local, total = 0;
-  for (int i = 0; i < bs / kWave; ++i) {
-    if (i < w) base += sm.wsum[i];
-    total += sm.wsum[i];
-  }
-  uint64_t n = level == 1 ? total : st->n;
-  if (level == 1 && n == 0) {
-    __syncthreads();
-    if (t == 0) {
-      st->n = 0;
-      st->done = 1;
-      if (qout) {
-        qout[0] = qout[1] = __builtin_nan("");
-        qout[2] = 0.0;
-      }
-      out->median = __builtin_nan("");
-      if (write_counts) {
-        out->count = 0;
-        out->nan_count = volume;
-        out->status = TSA_OK;
-      }
-    }
-    return;
-  }
-  uint64_t k = st->k;
-  if (level == 1) {
-    if (st->rank_mode) {
-      const double kk = floor(st->q * (double)(n - 1));
-      k = kk <= 0.0 ? 0 : kk >= (double)(n - 1) ? n - 1 : (uint64_t)kk;
-    } else {
-      k = (n - 1) / 2;
-    }
-  }
-  __syncthreads();  // every thread has read st before it changes
-  if (local > 0 && k >= base && k < base + local) {
-    uint64_t cum = base;
-    int d = b0;
-    for (int i = 0; i < per; ++i) {
-      const uint64_t h = (b0 + i < nb) ? hist[b0 + i] : 0;
-      if (k < cum + h) {
-        d = b0 + i;
-        break;
-      }
-      cum += h;
-    }
-    const uint64_t bucket = hist[d];
-    const uint32_t prefix = (level == 1 ? 0u : st->prefix) | ((uint32_t)d << shift);
-    st->n = n;
-    st->k = k - cum;
-    st->bucket_n = bucket;
-    st->prefix = prefix;
-    st->level = level;
-    if (level == 1) st->compact = bucket <= st->cand_cap ? 1u : 0u;
-    const bool exact = level == 3 || (dtype == 1 && level == 2);
-    const bool complete = exact || (st->levels >= 1 && (uint32_t)level >= st->levels);
-    if (complete) {
-      st->done = 1;
-      st->result_key = prefix;
-      if (qout) {
-        // the bucket [prefix, prefix | rest] holds the rank: its smallest value
-        // and its width bound the early answer
-        uint32_t rest = level == 1 ? 0x000FFFFFu : level == 2 ? 0xFFu : 0u;
-        if (dtype == 1) rest &= 0xFFFF0000u;
-        double lo = value_of_key(prefix, dtype), hi = value_of_key(prefix | rest, dtype);
-        if (lo != lo) lo = -__builtin_inf();
-        if (hi != hi) hi = __builtin_inf();
-        qout[0] = lo;
-        qout[1] = exact ? 0.0 : hi - lo;
-        qout[2] = (double)n;
-      }
-      out->median = value_of_key(prefix, dtype);
-      if (write_counts) {
-        out->count = n;
-        out->nan_count = volume - n;
-        out->status = TSA_OK;
-      }
-    }
-    sm.found = 1;
-  }
-  __syncthreads();
-  if (t == 0 && !sm.found) {  // inconsistent histogram: never expected
-    st->done = 1;
-    out->median = __builtin_nan("");
-    out->status = TSA_EDEVICE;
-  }
+  merge_moments(parts, np, dtype, volume, out, merge_scratch(sm), n, a, b, dtype == 0);
 }
 
 __global__ __launch_bounds__(1024) void k_select(int level, const uint64_t* __restrict__ hist, SelState* st,
@@ -449,9 +493,9 @@ TSA_DEV void median_of_state(const SelState* med, float& mf, int32_t& mi) {
 
 template <int DT, bool VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_mlevel1(Geom g, uint32_t rshift, const SelState* __restrict__ med,
-                                                  uint64_t* __restrict__ hist1) {
+                                                  SelState* __restrict__ st, uint64_t* __restrict__ hist1, Tail tl) {
   extern __shared__ uint32_t lds[];
-  if (!med->done || med->n == 0) return;
+  if (!med->done || med->n == 0) return;  // no value: st is left unfinished
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
   float mf;
@@ -461,14 +505,15 @@ __global__ __launch_bounds__(1024) void k_mlevel1(Geom g, uint32_t rshift, const
   walk<DT, VEC, kUnroll, NT>(g, a);
   __syncthreads();
   lds_flush(lds, kBins1, rshift, hist1);
+  select_tail(1, hist1, st, tl);
 }
 
 template <int DT, bool VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_mlevel2(Geom g, const SelState* __restrict__ med, SelState* __restrict__ st,
-                                                  uint64_t* __restrict__ hist2, uint32_t* __restrict__ cand) {
+                                                  uint64_t* __restrict__ hist2, uint32_t* __restrict__ cand, Tail tl) {
   __shared__ uint32_t lds[kBins2];
   __shared__ CandShared cs;
-  if (st->done) return;
+  if (st->level != 1 || st->done) return;
   lds_zero(lds, kBins2);
   __syncthreads();
   float mf;
@@ -481,13 +526,31 @@ __global__ __launch_bounds__(1024) void k_mlevel2(Geom g, const SelState* __rest
   a.inner.finish();
   __syncthreads();
   lds_flush(lds, kBins2, 0, hist2);
+  select_tail(2, hist2, st, tl);
+}
+
+// out[0..2] = (median, MAD, count); NaN, NaN, 0 without a valid voxel.
+TSA_DEV void mad_finish(const SelState* med, const SelState* st, int dtype, double* out) {
+  if (med->n == 0 || !med->done || !st->done) {
+    out[0] = out[1] = __builtin_nan("");
+    out[2] = (double)med->n;
+    return;
+  }
+  out[0] = value_of_key(med->result_key, dtype);
+  out[1] = (double)__uint_as_float(f32bits_of_key(st->result_key));
+  out[2] = (double)med->n;
 }
 
 template <int DT, bool VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_mlevel3(Geom g, const SelState* __restrict__ med, SelState* __restrict__ st,
-                                                  uint64_t* __restrict__ hist3, const uint32_t* __restrict__ cand) {
+                                                  uint64_t* __restrict__ hist3, const uint32_t* __restrict__ cand,
+                                                  Tail tl, int med_dtype, double* __restrict__ out) {
   __shared__ uint32_t lds[kBins3];
-  if (st->done) return;
+  __shared__ SelectShared ssm;
+  if (st->level != 2 || st->done) {  // the same for every block: the state was left by earlier launches
+    if (blockIdx.x == 0 && threadIdx.x == 0) mad_finish(med, st, med_dtype, out);
+    return;
+  }
   lds_zero(lds, kBins3);
   __syncthreads();
   const uint32_t p2 = st->prefix >> kShift2;
@@ -506,20 +569,10 @@ __global__ __launch_bounds__(1024) void k_mlevel3(Geom g, const SelState* __rest
   }
   __syncthreads();
   lds_flush(lds, kBins3, 0, hist3);
-}
-
-// out[0..2] = (median, MAD, count); NaN, NaN, 0 without a valid voxel.
-__global__ void k_mad_finish(const SelState* __restrict__ med, const SelState* __restrict__ st, int dtype,
-                             double* out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  if (med->n == 0 || !med->done || !st->done) {
-    out[0] = out[1] = __builtin_nan("");
-    out[2] = (double)med->n;
-    return;
-  }
-  out[0] = value_of_key(med->result_key, dtype);
-  out[1] = (double)__uint_as_float(f32bits_of_key(st->result_key));
-  out[2] = (double)med->n;
+  if (!last_block(tl.arrive + 2)) return;
+  select_level(3, hist3, st, tl.dtype, tl.volume, tl.out, false, ssm);
+  __syncthreads();
+  if (threadIdx.x == 0) mad_finish(med, st, med_dtype, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -538,54 +591,15 @@ struct PassA {
   TSA_DEV void chunk() {}
 };
 
-// The loads run a chunk ahead (walk_stream): 1024x1024x1280 voxels (5.4 GB)
-// 0.85 -> 0.83 ms, 6.4 TB/s.  Pass B loses by it (0.96 -> 1.15 ms: the second
-// set of vectors costs it a block per compute unit); the histogram, moments
-// and level passes gain nothing.
-template <int DT, bool VEC, bool NT>
-__global__ __launch_bounds__(1024) void k_pass_a(Geom g, uint32_t rshift, Partial* __restrict__ parts,
-                                                 uint64_t* __restrict__ hist1, uint64_t* __restrict__ hcopy,
-                                                 uint32_t hcopy_n) {
-  extern __shared__ uint32_t lds[];
-  __shared__ MomShared sm;
-  // pass B's histogram copies start at zero (cleared here, not by a launch of their own)
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < hcopy_n; i += gridDim.x * blockDim.x) hcopy[i] = 0ull;
-  lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
-  __syncthreads();
-  PassA<DT> a{MomAcc<DT, false>{}, Digit1Acc<DT>{lds, rshift, threadIdx.x & ((1u << rshift) - 1u)}};
-  walk_stream<DT, VEC, kUnroll, NT>(g, a);
-  // every valid value incremented one first-digit counter: the block's count
-  // is their total (each lane adds a strided share; the partial sums them)
-  __syncthreads();
-  uint32_t c = 0;
-  for (uint32_t i = threadIdx.x; i < ((uint32_t)kBins1 << rshift); i += blockDim.x) c += lds[i];
-  a.mom.cnt = c;
-  block_store_partial(a.mom, sm, parts + blockIdx.x);
-  __syncthreads();
-  lds_flush(lds, kBins1, rshift, hist1 + (size_t)(blockIdx.x % kHistCopies) * kBins1);
-}
-
-__global__ __launch_bounds__(1024) void k_mid(const Partial* __restrict__ parts, int np, int dtype, uint64_t volume,
-                                              int32_t nbins, uint64_t* __restrict__ hist1, SelState* st,
-                                              tsa_result* out) {
-  __shared__ MergeShared msm;
+// Pass A's last block: merges the moments, fixes the histogram's range and the
+// shift of the second moment, and chooses the first digit.  lds: 8 kBins1
+// bytes and 32 a thread (the larger).
+TSA_DEV void mid_tail(const Partial* parts, int np, int dtype, uint64_t volume, int32_t nbins,
+                      const uint64_t* __restrict__ hist1, SelState* st, tsa_result* out, uint64_t* lds) {
   __shared__ SelectShared ssm;
-  // pass A's blocks added into kHistCopies copies of the first-digit counts: summed into the first
-  static_assert(kBins1 % 1024 == 0, "k_mid runs as one block of 1024 threads, four bins a thread");
-  uint64_t c[kBins1 / 1024];
-#pragma unroll
-  for (int j = 0; j < kBins1 / 1024; ++j) {  // every load issued before the first add
-    const uint32_t b = threadIdx.x + 1024u * j;
-    c[j] = hist1[b];
-#pragma unroll
-    for (int k = 1; k < kHistCopies; ++k) c[j] += hist1[(size_t)k * kBins1 + b];
-  }
-#pragma unroll
-  for (int j = 0; j < kBins1 / 1024; ++j) hist1[threadIdx.x + 1024u * j] = c[j];
-  __syncthreads();
   uint64_t n;
   uint32_t kmin, kmax;
-  merge_moments(parts, np, dtype, volume, out, msm, n, kmin, kmax);
+  merge_moments(parts, np, dtype, volume, out, merge_scratch((double*)lds), n, kmin, kmax);
   if (threadIdx.x == 0) {
     uint32_t ok = 0;
     float lo = 0.f, hi = 0.f, scale = 0.f;
@@ -617,8 +631,24 @@ __global__ __launch_bounds__(1024) void k_mid(const Partial* __restrict__ parts,
     out->flags = ok ? 0 : TSA_FLAG_HIST_SKIPPED;
     out->median = __builtin_nan("");
   }
+  // pass A's blocks added into kHistCopies copies of the first-digit counts: summed here
+  static_assert(kBins1 % 1024 == 0, "blocks of 256, 512 or 1024 threads share the bins evenly");
+  for (uint32_t b = threadIdx.x; b < (uint32_t)kBins1; b += 4 * blockDim.x) {
+    uint64_t c[4][kHistCopies];  // every load issued before the first add
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int k = 0; k < kHistCopies; ++k) c[j][k] = hist1[(size_t)k * kBins1 + b + j * blockDim.x];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint64_t x = 0;
+#pragma unroll
+      for (int k = 0; k < kHistCopies; ++k) x += c[j][k];
+      lds[b + j * blockDim.x] = x;
+    }
+  }
   __syncthreads();
-  select_level(1, hist1, st, dtype, volume, out, false, ssm);
+  select_level(1, lds, st, dtype, volume, out, false, ssm);
   __syncthreads();
   if (threadIdx.x == 0) {
     // many bins: pass B counts the kWinBins bins around the median's first-digit
@@ -634,6 +664,39 @@ __global__ __launch_bounds__(1024) void k_mid(const Partial* __restrict__ parts,
     }
     st->win0 = w0;
   }
+}
+
+// The loads run a chunk ahead (walk_stream): 1024x1024x1280 voxels (5.4 GB)
+// 0.85 -> 0.83 ms, 6.4 TB/s.  Pass B loses by it (0.96 -> 1.15 ms: the second
+// set of vectors costs it a block per compute unit); the histogram, moments
+// and level passes gain nothing.
+template <int DT, bool VEC, bool NT>
+__global__ __launch_bounds__(1024) void k_pass_a(Geom g, uint32_t rshift, Partial* __restrict__ parts,
+                                                 uint64_t* __restrict__ hist1, uint64_t* __restrict__ hcopy,
+                                                 uint32_t hcopy_n, SelState* __restrict__ st,
+                                                 tsa_result* __restrict__ out, uint64_t volume, int32_t nbins,
+                                                 Arrive* arrive) {
+  extern __shared__ __align__(16) uint32_t lds[];
+  __shared__ MomShared sm;
+  __shared__ Partial sm_part;
+  // pass B's histogram copies start at zero (cleared here, not by a launch of their own)
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < hcopy_n; i += gridDim.x * blockDim.x) hcopy[i] = 0ull;
+  lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
+  __syncthreads();
+  PassA<DT> a{MomAcc<DT, false>{}, Digit1Acc<DT>{lds, rshift, threadIdx.x & ((1u << rshift) - 1u)}};
+  walk_stream<DT, VEC, kUnroll, NT>(g, a);
+  // every valid value incremented one first-digit counter: the block's count
+  // is their total (each lane adds a strided share; the partial sums them)
+  __syncthreads();
+  uint32_t c = 0;
+  for (uint32_t i = threadIdx.x; i < ((uint32_t)kBins1 << rshift); i += blockDim.x) c += lds[i];
+  a.mom.cnt = c;
+  block_store_partial(a.mom, sm, &sm_part);  // thread 0's
+  if (threadIdx.x == 0) publish_partial(sm_part, parts + blockIdx.x);
+  __syncthreads();
+  lds_flush(lds, kBins1, rshift, hist1 + (size_t)(blockIdx.x % kHistCopies) * kBins1);
+  if (last_block(arrive))
+    mid_tail(parts, (int)gridDim.x, DT, volume, nbins, hist1, st, out, (uint64_t*)lds);
 }
 
 template <int DT>
@@ -653,17 +716,47 @@ struct PassB {
   TSA_DEV void chunk() {}
 };
 
+// Pass B's last block: M2 about the shift c, M2 = sum (x-c)^2 - n (mean - c)^2,
+// the block partials added in a fixed order (strided per thread, then a
+// pairwise tree; sq: 8 bytes a thread), and the second digit.
+TSA_DEV void pass_b_tail(const Partial* parts2, SelState* st, const uint64_t* hist2, bool var_on, double* sq,
+                         const Tail& tl) {
+  __shared__ SelectShared ssm;
+  if (!last_block(tl.arrive + 1)) return;
+  if (var_on) {
+    const int t = threadIdx.x, bs = blockDim.x;
+    double q = 0.0;
+    for (int i = t; i < (int)gridDim.x; i += bs) q += parts2[i].q;
+    sq[t] = q;
+    __syncthreads();
+    for (int s2 = bs / 2; s2 > 0; s2 >>= 1) {
+      if (t < s2) sq[t] += sq[t + s2];
+      __syncthreads();
+    }
+    if (t == 0) {
+      const double n = (double)tl.out->count;
+      const double dm = tl.out->mean - (double)st->shift;
+      double m2 = sq[0] - n * dm * dm;
+      if (m2 < 0.0) m2 = 0.0;  // rounding below zero; NaN (infinite values) stays
+      tl.out->m2 = m2;
+      tl.out->std = sqrt(m2 / n);
+    }
+  }
+  select_level(2, hist2, st, tl.dtype, tl.volume, tl.out, false, ssm);
+}
+
 template <int DT, bool VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t rshift, uint32_t stage,
                                                  SelState* __restrict__ st,
                                                  uint64_t* __restrict__ counts, uint64_t* __restrict__ outl,
                                                  uint64_t* __restrict__ hist2, uint32_t* __restrict__ cand,
-                                                 Partial* __restrict__ parts2) {
+                                                 Partial* __restrict__ parts2, Tail tl) {
   // dynamic LDS: [nbins << rshift] histogram, [kBins2] level-2 digits, then the
   // candidate staging of the block's waves
-  extern __shared__ uint32_t lds[];
+  extern __shared__ __align__(16) uint32_t lds[];
   __shared__ uint32_t osm[32];
   __shared__ MomShared sm;
+  __shared__ Partial sm_part;
   const uint32_t hsize = ((uint32_t)nbins << rshift) + kTrash;
   uint32_t* l2 = lds + hsize;
   const bool hist_on = st->hist_ok != 0;
@@ -679,12 +772,15 @@ __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t
   walk<DT, VEC, kUnroll, NT>(g, b);
   b.l2.finish();
   __syncthreads();
-  // into one of kHistCopies copies (counts holds them nbins apart), summed by k_var_finish
+  // into one of kHistCopies copies (counts holds them nbins apart), summed by k_level3
   if (hist_on) lds_flush(lds, (uint32_t)nbins, rshift, counts + (size_t)(blockIdx.x % kHistCopies) * (uint32_t)nbins);
   if (sel_on) lds_flush(l2, kBins2, 0, hist2);
   // values lie in their own [min, max]: the outlier counters keep their zeros
-
-  if (var_on) block_store_var(b.var, sm, parts2 + blockIdx.x);
+  if (var_on) {
+    block_store_var(b.var, sm, &sm_part);  // thread 0's
+    if (threadIdx.x == 0) publish_partial(sm_part, parts2 + blockIdx.x);
+  }
+  pass_b_tail(parts2, st, hist2, var_on, (double*)lds, tl);
 }
 
 // Pass B with a window of kWinBins 32-bit LDS counters (more bins than fit):
@@ -710,10 +806,12 @@ struct PassBWin {
 template <int DT, bool VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_bwin(Geom g, int32_t nbins, SelState* __restrict__ st,
                                                     uint64_t* __restrict__ counts, uint64_t* __restrict__ hist2,
-                                                    uint32_t* __restrict__ cand, Partial* __restrict__ parts2) {
+                                                    uint32_t* __restrict__ cand, Partial* __restrict__ parts2,
+                                                    Tail tl) {
   // dynamic LDS: [kWinBins] window counters, [kBins2] level-2 digits, candidate staging
-  extern __shared__ uint32_t lds[];
+  extern __shared__ __align__(16) uint32_t lds[];
   __shared__ MomShared sm;
+  __shared__ Partial sm_part;
   uint32_t* l2 = lds + kWinBins;
   const bool hist_on = st->hist_ok != 0;
   const bool sel_on = st->done == 0;
@@ -737,7 +835,11 @@ __global__ __launch_bounds__(1024) void k_pass_bwin(Geom g, int32_t nbins, SelSt
     }
   }
   if (sel_on) lds_flush(l2, kBins2, 0, hist2);
-  if (var_on) block_store_var(b.var, sm, parts2 + blockIdx.x);
+  if (var_on) {
+    block_store_var(b.var, sm, &sm_part);  // thread 0's
+    if (threadIdx.x == 0) publish_partial(sm_part, parts2 + blockIdx.x);
+  }
+  pass_b_tail(parts2, st, hist2, var_on, (double*)lds, tl);
 }
 
 // Pass B with 16-bit histogram counters (nbins too large for 32-bit LDS
@@ -765,10 +867,11 @@ template <int DT, bool VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_b16(Geom g, int32_t nbins, uint32_t epoch, SelState* __restrict__ st,
                                                    uint64_t* __restrict__ counts, uint64_t* __restrict__ outl,
                                                    uint64_t* __restrict__ hist2, uint32_t* __restrict__ cand,
-                                                   Partial* __restrict__ parts2) {
-  extern __shared__ uint32_t lds[];  // [(nbins+1)/2] 16-bit counter pairs, then [kBins2] level-2 digits
+                                                   Partial* __restrict__ parts2, Tail tl) {
+  extern __shared__ __align__(16) uint32_t lds[];  // [(nbins+1)/2] 16-bit counter pairs, then [kBins2] level-2 digits
   __shared__ uint32_t osm[32];
   __shared__ MomShared sm;
+  __shared__ Partial sm_part;
   __shared__ CandShared cs;
   const uint32_t hwords = ((uint32_t)nbins + 1u) >> 1;
   uint32_t* l2 = lds + hwords;
@@ -788,42 +891,11 @@ __global__ __launch_bounds__(1024) void k_pass_b16(Geom g, int32_t nbins, uint32
   __syncthreads();
   if (sel_on) lds_flush(l2, kBins2, 0, hist2);
   if (hist_on) block_add_outliers(b.h.below, b.h.above, outl, osm);
-  if (var_on) block_store_var(b.var, sm, parts2 + blockIdx.x);
-}
-
-// M2 about the shift c: M2 = sum (x-c)^2 - n (mean - c)^2, block partials
-// added in a fixed order (strided per thread, then a pairwise tree).
-__global__ __launch_bounds__(1024) void k_var_finish(const Partial* __restrict__ parts2, int np,
-                                                     const SelState* __restrict__ st, tsa_result* out,
-                                                     const uint64_t* __restrict__ hcopy, int32_t nbins,
-                                                     uint64_t* __restrict__ counts) {
-  __shared__ double sq[1024];
-  if (hcopy) {  // the histogram from pass B's kHistCopies copies
-    for (uint32_t b = threadIdx.x; b < (uint32_t)nbins; b += blockDim.x) {
-      uint64_t c = 0;
-#pragma unroll
-      for (int k = 0; k < kHistCopies; ++k) c += hcopy[(size_t)k * (uint32_t)nbins + b];
-      counts[b] = c;
-    }
+  if (var_on) {
+    block_store_var(b.var, sm, &sm_part);  // thread 0's
+    if (threadIdx.x == 0) publish_partial(sm_part, parts2 + blockIdx.x);
   }
-  if (!st->var_on) return;
-  const int t = threadIdx.x, bs = blockDim.x;
-  double q = 0.0;
-  for (int i = t; i < np; i += bs) q += parts2[i].q;
-  sq[t] = q;
-  __syncthreads();
-  for (int s2 = bs / 2; s2 > 0; s2 >>= 1) {
-    if (t < s2) sq[t] += sq[t + s2];
-    __syncthreads();
-  }
-  if (t == 0) {
-    const double n = (double)out->count;
-    const double dm = out->mean - (double)st->shift;
-    double m2 = sq[0] - n * dm * dm;
-    if (m2 < 0.0) m2 = 0.0;  // rounding below zero; NaN (infinite values) stays
-    out->m2 = m2;
-    out->std = sqrt(m2 / n);
-  }
+  pass_b_tail(parts2, st, hist2, var_on, (double*)lds, tl);
 }
 
 // ---------------------------------------------------------------------------
@@ -979,11 +1051,13 @@ static int pass_grid(const Geom& g, bool vec, int block, int maxblocks) {
 
 // Workspace layout of the single-region calls.
 struct WsLayout {
-  size_t partials, partials2, hist1, hist2, hist3, state, state2, result, outl, hcopy, cand, total;
+  size_t partials, partials2, arrive, hist1, hist2, hist3, state, state2, result, outl, hcopy, cand, total;
   uint32_t cand_cap;
 };
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+constexpr int kArrives = 6;  // launches of a call that end in one block's work, at most
 
 // cand_limit: most candidate keys the layout may hold (the fixed scratch of
 // tsa_stats_static); a median bucket above the capacity takes a third pass.
@@ -994,6 +1068,9 @@ static WsLayout ws_layout(int64_t volume, int64_t cand_limit = INT64_MAX) {
   o = align256(o + sizeof(Partial) * kMaxBlocks);
   L.partials2 = o;
   o = align256(o + sizeof(Partial) * kMaxBlocks);
+  L.arrive = o;
+  o = align256(o + 2 * sizeof(Partial) * 256);  // room for Arrive[kArrives]
+  static_assert(sizeof(Arrive) * kArrives <= 2 * sizeof(Partial) * 256, "arrival counters");
   L.hist1 = o;
   o = align256(o + 8 * (size_t)kBins1 * kHistCopies);
   L.hist2 = o;
@@ -1026,16 +1103,15 @@ size_t single_ws_bytes(int64_t volume) { return ws_layout(volume).total; }
 
 static int launch_ok() { return hipGetLastError() == hipSuccess ? TSA_OK : TSA_EDEVICE; }
 
-static void fill32(void* p, size_t words, uint32_t v, hipStream_t s) {
-  if (words == 0) return;
-  int blocks = (int)((words + 255) / 256);
-  if (blocks > 1024) blocks = 1024;
-  TSA_TRACED("fill", s, hipLaunchKernelGGL(k_fill32, dim3(blocks), dim3(256), 0, s, (uint32_t*)p, (uint64_t)words, v));
-}
-
 // One launch for up to kMaxFills disjoint (words, value) ranges.
-static void fill_set(std::initializer_list<FillRange> ranges, hipStream_t s) {
+static void fill_set(std::initializer_list<FillRange> ranges, hipStream_t s, SelState* st = nullptr,
+                     const SelState& init = SelState{}, SelState* st2 = nullptr,
+                     const SelState& init2 = SelState{}) {
   FillSet f{};
+  f.st[0] = st;
+  f.init[0] = init;
+  f.st[1] = st2;
+  f.init[1] = init2;
   uint64_t most = 0;
   for (const FillRange& r : ranges) {
     if (r.n == 0) continue;
@@ -1137,44 +1213,57 @@ static uint32_t rep_shift_for(int nbins, size_t lds_budget) {
   return r;
 }
 
-// Zero the level histograms and the selection state, set the capacity, and
-// clear the caller's output counters (d_counts: nbins u64, outl: 2 u64; null
-// for none), all in one launch.
-static void reset_select(const Prep& P, uint64_t* d_counts = nullptr, int32_t nbins = 0, uint64_t* outl = nullptr) {
-  char* lo = P.ws + P.L.hist1;
-  char* cap = P.ws + P.L.state + offsetof(SelState, cand_cap);
-  char* hi = P.ws + P.L.state + sizeof(SelState);
-  static_assert(offsetof(SelState, cand_cap) % 4 == 0, "word-aligned capacity");
-  fill_set({FillRange{(uint32_t*)lo, (uint64_t)(cap - lo) / 4, 0u, 0u},
-            FillRange{(uint32_t*)cap, 1u, P.L.cand_cap, 0u},
-            FillRange{(uint32_t*)(cap + 4), (uint64_t)(hi - cap - 4) / 4, 0u, 0u},
+// The arrival counters of the call's launches from number `first` on.
+static Arrive* arrive_of(const Prep& P, int first) { return (Arrive*)(P.ws + P.L.arrive) + first; }
+
+// The selection state a call starts from: the lower median, or quantile q
+// selected to `levels` digits.
+static SelState first_state(const Prep& P) {
+  SelState x{};
+  x.cand_cap = P.L.cand_cap;
+  return x;
+}
+static SelState first_state(const Prep& P, double q, int32_t levels) {
+  SelState x = first_state(P);
+  x.q = q;
+  x.rank_mode = 1u;
+  x.levels = (uint32_t)levels;
+  return x;
+}
+
+// Zero the arrival counters and the level histograms, set the selection state, and clear the caller's
+// output counters (d_counts: nbins u64, outl: 2 u64; null for none), all in
+// one launch.
+static void reset_select(const Prep& P, const SelState& init, uint64_t* d_counts = nullptr, int32_t nbins = 0,
+                         uint64_t* outl = nullptr) {
+  fill_set({FillRange{(uint32_t*)(P.ws + P.L.arrive), (uint64_t)(P.L.state - P.L.arrive) / 4, 0u, 0u},
             FillRange{(uint32_t*)d_counts, d_counts ? (uint64_t)nbins * 2 : 0u, 0u, 0u},
             FillRange{(uint32_t*)outl, outl ? 4u : 0u, 0u, 0u}},
-           P.s);
+           P.s, (SelState*)(P.ws + P.L.state), init);
 }
 
 template <int DT, bool VEC, bool NT>
 static int launch_pass_b16(const Prep& P, int block, int grid, size_t lds, int32_t nbins, uint32_t epoch,
                            SelState* stp, uint64_t* d_counts, uint64_t* outl, uint64_t* h2, uint32_t* cand,
-                           Partial* parts2) {
+                           Partial* parts2, const Tail& tl) {
   if (lds > 65536 && hipFuncSetAttribute((const void*)k_pass_b16<DT, VEC, NT>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return TSA_EDEVICE;
   TSA_TRACED("pass_b16", P.s,
              hipLaunchKernelGGL((k_pass_b16<DT, VEC, NT>), dim3(grid), dim3(block), lds, P.s, P.g, nbins, epoch, stp,
-                                d_counts, outl, h2, cand, parts2));
+                                d_counts, outl, h2, cand, parts2, tl));
   return TSA_OK;
 }
 
 template <int DT, bool VEC, bool NT>
 static int launch_pass_bwin(const Prep& P, int block, int grid, size_t lds, int32_t nbins, SelState* stp,
-                            uint64_t* d_counts, uint64_t* h2, uint32_t* cand, Partial* parts2) {
+                            uint64_t* d_counts, uint64_t* h2, uint32_t* cand, Partial* parts2, const Tail& tl) {
   if (hipFuncSetAttribute((const void*)k_pass_bwin<DT, VEC, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)lds) != hipSuccess)
     return TSA_EDEVICE;
   TSA_TRACED("pass_bwin", P.s,
              hipLaunchKernelGGL((k_pass_bwin<DT, VEC, NT>), dim3(grid), dim3(block), lds, P.s, P.g, nbins, stp,
-                                d_counts, h2, cand, parts2));
+                                d_counts, h2, cand, parts2, tl));
   return TSA_OK;
 }
 
@@ -1259,22 +1348,27 @@ int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, floa
   return run_histogram_wide(cube, P.g, P.vec, P.grid, P.block, lo, hi, scale, nbins, d_counts, outl, P.s);
 }
 
-static int launch_median_tail(const tsa_cube* cube, const Prep& P, tsa_result* d_out, bool write_counts,
-                              double* qout = nullptr) {
+// The three passes of a selection over the region, each choosing its digit in
+// its last block.
+static int launch_selection(const tsa_cube* cube, const Prep& P, const Tail& tl) {
   SelState* stp = (SelState*)(P.ws + P.L.state);
+  uint64_t* h1 = (uint64_t*)(P.ws + P.L.hist1);
   uint64_t* h2 = (uint64_t*)(P.ws + P.L.hist2);
   uint64_t* h3 = (uint64_t*)(P.ws + P.L.hist3);
   uint32_t* cand = (uint32_t*)(P.ws + P.L.cand);
-  TSA_TRACED("select", P.s,
-             hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 2, (const uint64_t*)h2, stp, cube->dtype,
-                                (uint64_t)P.volume, d_out, (int)write_counts, qout));
+  const uint32_t rs = rep_shift_for(kBins1, 32768);
+  TSA_TRACED("level1", P.s,
+    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
+                 hipLaunchKernelGGL((k_level1<DT, VEC, NT>), dim3(P.grid), dim3(P.block),
+                                    (((size_t)kBins1 << rs) + kTrash) * 4, P.s, P.g, rs, stp, h1, tl)));
+  TSA_TRACED("level2", P.s,
+    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
+                 hipLaunchKernelGGL((k_level2<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, stp, h2, cand,
+                                    tl)));
   TSA_TRACED("level3", P.s,
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
                  hipLaunchKernelGGL((k_level3<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, stp, h3,
-                                    (const uint32_t*)cand, 1)));
-  TSA_TRACED("select", P.s,
-             hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 3, (const uint64_t*)h3, stp, cube->dtype,
-                                (uint64_t)P.volume, d_out, (int)write_counts, qout));
+                                    (const uint32_t*)cand, 1, tl, HistCopies{})));
   return launch_ok();
 }
 
@@ -1289,23 +1383,8 @@ int run_median(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out
   ask.rank = 1;
   ask.write_counts = 1;
   if (try_count16(cube, P, ask, &st)) return st;
-  reset_select(P);
-  SelState* stp = (SelState*)(P.ws + P.L.state);
-  uint64_t* h1 = (uint64_t*)(P.ws + P.L.hist1);
-  uint64_t* h2 = (uint64_t*)(P.ws + P.L.hist2);
-  uint32_t* cand = (uint32_t*)(P.ws + P.L.cand);
-  const uint32_t rs = rep_shift_for(kBins1, 32768);
-  TSA_TRACED("level1", P.s,
-    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 hipLaunchKernelGGL((k_level1<DT, VEC, NT>), dim3(P.grid), dim3(P.block), (((size_t)kBins1 << rs) + kTrash) * 4,
-                                    P.s, P.g, rs, h1)));
-  TSA_TRACED("select", P.s,
-             hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 1, (const uint64_t*)h1, stp, cube->dtype,
-                                (uint64_t)P.volume, d_out, 1, (double*)nullptr));
-  TSA_TRACED("level2", P.s,
-    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 hipLaunchKernelGGL((k_level2<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, stp, h2, cand)));
-  return launch_median_tail(cube, P, d_out, true);
+  reset_select(P, first_state(P));
+  return launch_selection(cube, P, Tail{d_out, nullptr, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 1});
 }
 
 // ---------------------------------------------------------------------------
@@ -1387,7 +1466,8 @@ int run_median_chunked(const tsa_cube* cube, tsa_result* d_out, void* d_ws, size
   if (st) return st;
   std::vector<Slab> slabs;
   if ((st = slabs_of(cube, chunk_voxels, P, &slabs))) return st;
-  reset_select(P);
+  reset_select(P, first_state(P));
+  const Tail tl{};  // a digit is chosen after its last slab
   SelState* stp = (SelState*)(P.ws + P.L.state);
   uint64_t* h1 = (uint64_t*)(P.ws + P.L.hist1);
   uint64_t* h2 = (uint64_t*)(P.ws + P.L.hist2);
@@ -1398,7 +1478,7 @@ int run_median_chunked(const tsa_cube* cube, tsa_result* d_out, void* d_ws, size
     TSA_TRACED("level1", P.s,
       TSA_DISPATCH(cube->dtype, sl.vec, tuning().nt,
                    hipLaunchKernelGGL((k_level1<DT, VEC, NT>), dim3(sl.grid), dim3(P.block),
-                                      (((size_t)kBins1 << rs) + kTrash) * 4, P.s, sl.g, rs, h1)));
+                                      (((size_t)kBins1 << rs) + kTrash) * 4, P.s, sl.g, rs, stp, h1, tl)));
   TSA_TRACED("select", P.s,
              hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 1, (const uint64_t*)h1, stp, cube->dtype,
                                 (uint64_t)P.volume, d_out, 1, (double*)nullptr));
@@ -1406,7 +1486,7 @@ int run_median_chunked(const tsa_cube* cube, tsa_result* d_out, void* d_ws, size
     TSA_TRACED("level2", P.s,
       TSA_DISPATCH(cube->dtype, sl.vec, tuning().nt,
                    hipLaunchKernelGGL((k_level2<DT, VEC, NT>), dim3(sl.grid), dim3(P.block), 0, P.s, sl.g, stp, h2,
-                                      cand)));
+                                      cand, tl)));
   TSA_TRACED("select", P.s,
              hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 2, (const uint64_t*)h2, stp, cube->dtype,
                                 (uint64_t)P.volume, d_out, 1, (double*)nullptr));
@@ -1414,7 +1494,8 @@ int run_median_chunked(const tsa_cube* cube, tsa_result* d_out, void* d_ws, size
     TSA_TRACED("level3", P.s,
       TSA_DISPATCH(cube->dtype, slabs[i].vec, tuning().nt,
                    hipLaunchKernelGGL((k_level3<DT, VEC, NT>), dim3(slabs[i].grid), dim3(P.block), 0, P.s,
-                                      slabs[i].g, stp, h3, (const uint32_t*)cand, i == 0 ? 1 : 0)));
+                                      slabs[i].g, stp, h3, (const uint32_t*)cand, i == 0 ? 1 : 0, tl,
+                                      HistCopies{})));
   TSA_TRACED("select", P.s,
              hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 3, (const uint64_t*)h3, stp, cube->dtype,
                                 (uint64_t)P.volume, d_out, 1, (double*)nullptr));
@@ -1531,6 +1612,19 @@ int run_stats_static(const tsa_cube* cube, const tsa_region* region, int32_t nbi
 size_t stats_static_scratch_bytes() { return kStaticScratchBytes; }
 int64_t stats_static_cand_keys() { return static_cand_limit(); }
 
+// The trio's last launch: the third digit (over the candidates, rarely over the
+// region again) and the sum of the histogram's copies.
+static int launch_last_digit(const tsa_cube* cube, const Prep& P, const Tail& tl, const HistCopies& hc) {
+  SelState* stp = (SelState*)(P.ws + P.L.state);
+  uint64_t* h3 = (uint64_t*)(P.ws + P.L.hist3);
+  const uint32_t* cand = (const uint32_t*)(P.ws + P.L.cand);
+  TSA_TRACED("level3", P.s,
+    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
+                 hipLaunchKernelGGL((k_level3<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, stp, h3, cand,
+                                    1, tl, hc)));
+  return launch_ok();
+}
+
 static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t nbins, tsa_result* d_out,
                          uint64_t* d_counts, uint64_t* d_outliers, void* d_ws, size_t ws_bytes, tsa_stream_t stream,
                          int64_t cand_limit) {
@@ -1554,7 +1648,7 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
   ask.moments = 1;
   ask.rank = 1;
   if (try_count16(cube, P, ask, &st)) return st;
-  reset_select(P, d_counts, nbins, outl);
+  reset_select(P, first_state(P), d_counts, nbins, outl);
   Partial* parts = (Partial*)(P.ws + P.L.partials);
   SelState* stp = (SelState*)(P.ws + P.L.state);
   uint64_t* h1 = (uint64_t*)(P.ws + P.L.hist1);
@@ -1562,16 +1656,16 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
   uint32_t* cand = (uint32_t*)(P.ws + P.L.cand);
   uint64_t* hcopy = (uint64_t*)(P.ws + P.L.hcopy);
   if (!wide && nbins > (int32_t)kCopyBinsMax) return TSA_ENOTSUP;  // cannot happen: the LDS bounds nbins first
+  const Tail tl{d_out, nullptr, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 0};
   const uint32_t rs1 = rep_shift_for(kBins1, 32768);
+  size_t lds_a = (((size_t)kBins1 << rs1) + kTrash) * 4;
+  if (lds_a < 8 * (size_t)kBins1) lds_a = 8 * (size_t)kBins1;  // its last block's sums (32 bytes a thread fit too)
   TSA_TRACED("pass_a", P.s,
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 hipLaunchKernelGGL((k_pass_a<DT, VEC, NT>), dim3(P.grid), dim3(P.block), (((size_t)kBins1 << rs1) + kTrash) * 4,
-                                    P.s, P.g, rs1, parts, h1, hcopy, wide ? 0u : (uint32_t)kHistCopies * (uint32_t)nbins)));
-  TSA_TRACED("mid", P.s,
-             hipLaunchKernelGGL(k_mid, dim3(1), dim3(1024), 0, P.s, (const Partial*)parts, P.grid, cube->dtype,
-                                (uint64_t)P.volume, nbins, h1, stp, d_out));
+                 hipLaunchKernelGGL((k_pass_a<DT, VEC, NT>), dim3(P.grid), dim3(P.block), lds_a, P.s, P.g, rs1, parts,
+                                    h1, hcopy, wide ? 0u : (uint32_t)kHistCopies * (uint32_t)nbins, stp, d_out,
+                                    (uint64_t)P.volume, nbins, arrive_of(P, 0))));
   Partial* parts2 = (Partial*)(P.ws + P.L.partials2);
-  int np2 = P.grid;
   if (!wide) {
     // replicas only as far as bpc blocks of pass B still share a compute unit
     // (its static LDS: candidate staging, moment reduction, outliers)
@@ -1593,25 +1687,21 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
     TSA_TRACED("pass_b", P.s,
       TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
                    hipLaunchKernelGGL((k_pass_b<DT, VEC, NT>), dim3(P.grid), dim3(P.block), ldsb, P.s, P.g, nbins,
-                                      rsb, stage, stp, hcopy, outl, h2, cand, parts2)));
+                                      rsb, stage, stp, hcopy, outl, h2, cand, parts2, tl)));
   } else {
     // one 1024-thread block per compute unit: a window of 32-bit counters when
     // the device grants the LDS, else 16-bit counters flushed in epochs
     const int blk = 1024;
     int grid = P.dev.cus;
     if (grid > P.grid) grid = P.grid;
-    np2 = grid;
     const size_t lds_win = ((size_t)kWinBins + kBins2 + (blk / kWave) * kWaveStage) * 4;
     if (lds_win + sizeof(MomShared) + 1024 <= P.dev.lds_per_block) {
       int stw = TSA_OK;
       TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
                    stw = (launch_pass_bwin<DT, VEC, NT>(P, blk, grid, lds_win, nbins, stp, d_counts, h2, cand,
-                                                        parts2)));
+                                                        parts2, tl)));
       if (stw) return stw;
-      TSA_TRACED("var_finish", P.s,
-                 hipLaunchKernelGGL(k_var_finish, dim3(1), dim3(1024), 0, P.s, (const Partial*)parts2, np2,
-                                    (const SelState*)stp, d_out, (const uint64_t*)nullptr, nbins, d_counts));
-      return launch_median_tail(cube, P, d_out, false);
+      return launch_last_digit(cube, P, tl, HistCopies{});
     }
     const int epv = P.vec ? (cube->dtype == TSA_F32 ? 4 : 8) : 1;
     const int64_t ep = (65535 - 16) / ((int64_t)blk * kUnroll * epv);
@@ -1619,23 +1709,10 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
     int st2 = TSA_OK;
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
                  st2 = (launch_pass_b16<DT, VEC, NT>(P, blk, grid, lds16, nbins, (uint32_t)ep, stp, d_counts, outl,
-                                                     h2, cand, parts2)));
+                                                     h2, cand, parts2, tl)));
     if (st2) return st2;
   }
-  TSA_TRACED("var_finish", P.s,
-             hipLaunchKernelGGL(k_var_finish, dim3(1), dim3(1024), 0, P.s, (const Partial*)parts2, np2,
-                                (const SelState*)stp, d_out, wide ? (const uint64_t*)nullptr : (const uint64_t*)hcopy,
-                                nbins, d_counts));
-  return launch_median_tail(cube, P, d_out, false);
-}
-
-
-__global__ void k_init_rank(SelState* st, double q, uint32_t mode, uint32_t levels) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    st->q = q;
-    st->rank_mode = mode;
-    st->levels = levels;
-  }
+  return launch_last_digit(cube, P, tl, wide ? HistCopies{} : HistCopies{hcopy, d_counts, nbins});
 }
 
 int run_quantile(const tsa_cube* cube, const tsa_region* region, double q, int32_t digits, double* d_out,
@@ -1650,26 +1727,9 @@ int run_quantile(const tsa_cube* cube, const tsa_region* region, double q, int32
   ask.q = q;
   ask.digits = digits;
   if (try_count16(cube, P, ask, &st)) return st;
-  reset_select(P);
-  SelState* stp = (SelState*)(P.ws + P.L.state);
+  reset_select(P, first_state(P, q, digits));
   tsa_result* scratch = (tsa_result*)(P.ws + P.L.result);
-  uint64_t* h1 = (uint64_t*)(P.ws + P.L.hist1);
-  uint64_t* h2 = (uint64_t*)(P.ws + P.L.hist2);
-  uint32_t* cand = (uint32_t*)(P.ws + P.L.cand);
-  TSA_TRACED("init", P.s, hipLaunchKernelGGL(k_init_rank, dim3(1), dim3(64), 0, P.s, stp, q, 1u, (uint32_t)digits));
-  const uint32_t rs = rep_shift_for(kBins1, 32768);
-  TSA_TRACED("level1", P.s,
-    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 hipLaunchKernelGGL((k_level1<DT, VEC, NT>), dim3(P.grid), dim3(P.block),
-                                    (((size_t)kBins1 << rs) + kTrash) * 4, P.s, P.g, rs, h1)));
-  TSA_TRACED("select", P.s,
-             hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 1, (const uint64_t*)h1, stp, cube->dtype,
-                                (uint64_t)P.volume, scratch, 0, d_out));
-  TSA_TRACED("level2", P.s,
-    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 hipLaunchKernelGGL((k_level2<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, stp, h2,
-                                    cand)));
-  return launch_median_tail(cube, P, scratch, false, d_out);
+  return launch_selection(cube, P, Tail{scratch, d_out, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 0});
 }
 
 int run_mad(const tsa_cube* cube, const tsa_region* region, double* d_out, void* d_ws, size_t ws_bytes,
@@ -1683,62 +1743,37 @@ int run_mad(const tsa_cube* cube, const tsa_region* region, double* d_out, void*
   ask.rank = 1;
   ask.mad = 1;
   if (try_count16(cube, P, ask, &st)) return st;
-  reset_select(P);
   SelState* med = (SelState*)(P.ws + P.L.state);
   SelState* sb = (SelState*)(P.ws + P.L.state2);
   tsa_result* scratch = (tsa_result*)(P.ws + P.L.result);
-  uint64_t* h1 = (uint64_t*)(P.ws + P.L.hist1);
-  uint64_t* h2 = (uint64_t*)(P.ws + P.L.hist2);
-  uint64_t* h3 = (uint64_t*)(P.ws + P.L.hist3);
   uint32_t* cand = (uint32_t*)(P.ws + P.L.cand);
-  {
-    char* b = (char*)sb;
-    const size_t c = offsetof(SelState, cand_cap);
-    fill_set({FillRange{(uint32_t*)b, c / 4, 0u, 0u}, FillRange{(uint32_t*)(b + c), 1u, P.L.cand_cap, 0u},
-              FillRange{(uint32_t*)(b + c + 4), (sizeof(SelState) - c - 4) / 4, 0u, 0u}},
-             P.s);
-  }
+  // the deviations' digit counts lie where the trio keeps its histogram copies
+  uint64_t* m1 = (uint64_t*)(P.ws + P.L.hcopy);
+  uint64_t* m2 = m1 + kBins1;
+  uint64_t* m3 = m2 + kBins2;
+  const SelState init = first_state(P);
+  fill_set({FillRange{(uint32_t*)(P.ws + P.L.arrive), (uint64_t)(P.L.state - P.L.arrive) / 4, 0u, 0u},
+            FillRange{(uint32_t*)m1, 2ull * (kBins1 + kBins2 + kBins3), 0u, 0u}},
+           P.s, med, init, sb, init);
   // 1. the lower median m
-  const uint32_t rs = rep_shift_for(kBins1, 32768);
-  TSA_TRACED("level1", P.s,
-    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 hipLaunchKernelGGL((k_level1<DT, VEC, NT>), dim3(P.grid), dim3(P.block),
-                                    (((size_t)kBins1 << rs) + kTrash) * 4, P.s, P.g, rs, h1)));
-  TSA_TRACED("select", P.s,
-             hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 1, (const uint64_t*)h1, med, cube->dtype,
-                                (uint64_t)P.volume, scratch, 0, (double*)nullptr));
-  TSA_TRACED("level2", P.s,
-    TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 hipLaunchKernelGGL((k_level2<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, med, h2,
-                                    cand)));
-  st = launch_median_tail(cube, P, scratch, false);
+  st = launch_selection(cube, P, Tail{scratch, nullptr, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 0});
   if (st) return st;
   // 2. the lower median of |x - m| (float keys whatever the cube's type)
-  fill32(h1, (P.L.state - P.L.hist1) / 4, 0u, P.s);
+  const Tail tl{scratch, nullptr, (uint64_t)P.volume, arrive_of(P, 3), 0, 0};
+  const uint32_t rs = rep_shift_for(kBins1, 32768);
   TSA_TRACED("mad_level1", P.s,
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
                  hipLaunchKernelGGL((k_mlevel1<DT, VEC, NT>), dim3(P.grid), dim3(P.block),
-                                    (((size_t)kBins1 << rs) + kTrash) * 4, P.s, P.g, rs, (const SelState*)med, h1)));
-  TSA_TRACED("select", P.s,
-             hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 1, (const uint64_t*)h1, sb, 0,
-                                (uint64_t)P.volume, scratch, 0, (double*)nullptr));
+                                    (((size_t)kBins1 << rs) + kTrash) * 4, P.s, P.g, rs, (const SelState*)med, sb, m1,
+                                    tl)));
   TSA_TRACED("mad_level2", P.s,
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
                  hipLaunchKernelGGL((k_mlevel2<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g,
-                                    (const SelState*)med, sb, h2, cand)));
-  TSA_TRACED("select", P.s,
-             hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 2, (const uint64_t*)h2, sb, 0,
-                                (uint64_t)P.volume, scratch, 0, (double*)nullptr));
+                                    (const SelState*)med, sb, m2, cand, tl)));
   TSA_TRACED("mad_level3", P.s,
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
                  hipLaunchKernelGGL((k_mlevel3<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g,
-                                    (const SelState*)med, sb, h3, (const uint32_t*)cand)));
-  TSA_TRACED("select", P.s,
-             hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, P.s, 3, (const uint64_t*)h3, sb, 0,
-                                (uint64_t)P.volume, scratch, 0, (double*)nullptr));
-  TSA_TRACED("mad_finish", P.s,
-             hipLaunchKernelGGL(k_mad_finish, dim3(1), dim3(64), 0, P.s, (const SelState*)med, (const SelState*)sb,
-                                cube->dtype, d_out));
+                                    (const SelState*)med, sb, m3, (const uint32_t*)cand, tl, cube->dtype, d_out)));
   return launch_ok();
 }
 

@@ -103,9 +103,9 @@ TSA_DEV void chan_merge(double& na, double& ma, double& qa, double nb, double mb
     na = n;
     return;
   }
-  const double d = mb - ma;
-  ma = ma + d * (nb / n);
-  qa = qa + qb + d * d * (na * nb / n);
+  const double d = mb - ma, f = nb / n;  // one division: a merge tree is a chain of them
+  ma = ma + d * f;
+  qa = qa + qb + d * d * (na * f);
   na = n;
 }
 
@@ -167,6 +167,15 @@ struct ShiftMomAcc {
   }
   TSA_DEV void chunk() {}
 };
+
+// Stores a partial where another block of the same launch may read it
+// (agent-scope atomic stores; see last_block).
+TSA_DEV void publish_partial(const Partial& p, Partial* out) {
+  const uint64_t* src = (const uint64_t*)&p;
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(Partial) / 8; ++i)
+    __hip_atomic_store((uint64_t*)out + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Reduce a block's lanes (fixed order) and store one Partial.
 struct alignas(16) MomShared {
@@ -720,6 +729,48 @@ TSA_DEV bool block_select_small(const uint32_t* hist, int nb, uint32_t k, SH& sh
 
 TSA_DEV double bvalue_of_key(uint32_t k, int dtype) {
   return dtype == 0 ? (double)__uint_as_float(f32bits_of_key(k)) : (double)i16_of_key(k);
+}
+
+// Every wave waits until its own global stores and atomics are acknowledged
+// (s_waitcnt vmcnt(0)) before the barrier after which one thread publishes
+// the block's work with an agent-scope release: a workgroup barrier alone
+// does not wait for other waves' writes to reach the L2 that the release
+// writes back.
+TSA_DEV void block_writes_done() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt 0; expcnt and lgkmcnt not waited for
+  __syncthreads();
+}
+
+// The blocks of a launch count themselves as they end; true in every thread of
+// the last one, which sees what all the others published.  One block's work on
+// a pass's results so needs no launch of its own.  Published is what agent-scope
+// atomics wrote (counters added to, publish_partial): they act at the device's
+// point of coherence, and every wave waits until its own are acknowledged
+// before its block counts itself, so no block pays an agent-scope release (each
+// writes back a whole L2: 20 us over a pass of 768 blocks).  Plain stores are
+// for the launches that follow.  Blocks that end together
+// queue on one counter (12 ns each, 9 us for 768), so they count in
+// kArriveGroups counters on lines of their own, and the last of each group in
+// a root.  All zero before the launch.
+constexpr uint32_t kArriveGroups = 16, kArriveLine = 32;  // words
+struct Arrive {
+  uint32_t word[(kArriveGroups + 1) * kArriveLine];
+};
+TSA_DEV bool last_block(Arrive* a) {
+  __shared__ uint32_t last;
+  block_writes_done();
+  if (threadIdx.x == 0) {
+    const uint32_t g = blockIdx.x % kArriveGroups, ng = gridDim.x < kArriveGroups ? gridDim.x : kArriveGroups;
+    const uint32_t mine = (gridDim.x - g + kArriveGroups - 1u) / kArriveGroups;
+    uint32_t r = 0;
+    if (__hip_atomic_fetch_add(a->word + g * kArriveLine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == mine)
+      r = __hip_atomic_fetch_add(a->word + kArriveGroups * kArriveLine, 1u, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT) + 1u == ng;
+    if (r) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    last = r;
+  }
+  __syncthreads();
+  return last != 0;
 }
 
 // ---- radix digits of the key (Section 4.3 replaced by radix selection) --------
