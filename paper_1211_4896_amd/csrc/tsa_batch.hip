@@ -123,7 +123,9 @@ __global__ __launch_bounds__(1024) void k_bauto(BArgs a) {
     if (!(r.x0 >= 0 && r.y0 >= 0 && r.z0 >= 0 && r.x1 <= a.nx && r.y1 <= a.ny && r.z1 <= a.nz && r.x0 < r.x1 &&
           r.y0 < r.y1 && r.z0 < r.z1))
       continue;
-    const uint64_t row = a.vec ? (uint64_t)((r.x1 + epv - 1) / epv - r.x0 / epv) : (uint64_t)(r.x1 - r.x0);
+    const uint64_t row = a.vec == 1   ? (uint64_t)((r.x1 + epv - 1) / epv - r.x0 / epv)
+                         : a.vec == 2 ? (uint64_t)((r.x1 - r.x0 + epv - 1) / epv)
+                                      : (uint64_t)(r.x1 - r.x0);
     local += row * (uint64_t)(r.y1 - r.y0) * (uint64_t)(r.z1 - r.z0);
   }
   local = wave_sum_u64(local);
@@ -166,7 +168,7 @@ __global__ void k_bplan(BArgs a) {
       g.volume = vol;
       g.ly = (uint32_t)ly;
       g.nrows = (uint32_t)nrows;
-      if (a.vec) {
+      if (a.vec == 1) {
         const int64_t c0 = r.x0 / epv, c1 = (r.x1 + epv - 1) / epv;
         g.v_origin = c0 + (a.nx / epv) * (r.y0 + a.ny * r.z0);
         g.vpr = (uint32_t)(c1 - c0);
@@ -177,6 +179,11 @@ __global__ void k_bplan(BArgs a) {
         g.vpr = (uint32_t)lx;
         g.head_skip = 0;
         g.last_valid = 1;
+        if (a.vec == 2) {
+          g.vpr = (uint32_t)((lx + epv - 1) / epv);
+          g.head_skip = lx < epv ? 0u : (uint32_t)(g.vpr * epv - lx);
+          g.last_valid = (uint32_t)(lx < epv ? lx : epv);
+        }
       }
       const uint32_t tu = a.tile_units ? a.tile_units : a.hdr->tile_units;
       uint64_t rpt = tu / g.vpr;
@@ -536,43 +543,11 @@ TSA_DEV void epilogue3(const BArgs& a, uint32_t q, BShared& sh) {
   __syncthreads();
 }
 
-// ---------------------------------------------------------------------------
-// per-tile accumulators
-// ---------------------------------------------------------------------------
-template <int DT>
-struct BPass1 {
-  MomAcc<DT, false> mom;  // the count is the digit histogram's total
-  Digit1Acc<DT> d1;
-  template <class T>
-  TSA_DEV void operator()(T raw, bool in) {
-    mom(raw, in);
-    d1(raw, in);
-  }
-  TSA_DEV void chunk() {}
-};
-
-template <int DT>
-struct BPass2 {
-  HistOwnAcc h;
-  Level2Acc<DT> l2;
-  VarAcc var;
-  bool hist_on, var_on;
-  template <class T>
-  TSA_DEV void operator()(T raw, bool in) {
-    if (hist_on) h(raw, in);
-    l2(raw, in);
-    if constexpr (DT == 0) {
-      if (var_on) var(raw, in);
-    }
-  }
-  TSA_DEV void chunk() {}
-};
-
-template <int DT, bool VEC, bool NT, class F>
+template <int DT, int VEC, bool NT, class F>
 TSA_DEV void walk_tile(const BArgs& a, const QGeom& g, uint32_t tile, F& f) {
   const uint32_t r0 = tile * g.rpt;
   const uint32_t nr = min(g.rpt, g.nrows - r0);
-  const int64_t epv = VEC ? (DT == 0 ? 4 : 8) : 1;
+  const int64_t epv = VEC == 1 ? (DT == 0 ? 4 : 8) : 1;
   const int64_t ys = a.nx / epv, zs = (a.nx / epv) * a.ny;
   walk_rows<DT, VEC, kBUnroll, NT>(a.base, g.v_origin, ys, zs, g.ly, g.ly_m, g.vpr, g.vpr_m, g.head_skip,
                                    g.last_valid, r0, nr, f);
@@ -585,7 +560,7 @@ TSA_DEV void walk_tile(const BArgs& a, const QGeom& g, uint32_t tile, F& f) {
 // one partial, the digit choices, the histogram formula, the candidate pool
 // -- so the results are the same bits; only the counters stay in LDS between
 // the passes instead of going through global memory and the epilogues.
-template <int DT, bool VEC, bool NT, class CS>
+template <int DT, int VEC, bool NT, class CS>
 TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t* lds) {
   const QGeom& g = a.geom[q];
   QState& s = a.st[q];
@@ -594,7 +569,7 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
   // pass 1: moments + first key digit
   lds_zero(lds, kBins1 + kTrash);
   __syncthreads();
-  BPass1<DT> f{MomAcc<DT, false>{}, Digit1Acc<DT>{lds, 0u, 0u}};
+  Pass1Acc<DT> f(lds, 0u);
   walk_tile<DT, VEC, NT>(a, g, 0u, f);
   __syncthreads();
   uint32_t c = 0;  // every valid value incremented one first-digit counter
@@ -640,7 +615,7 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
   }
   const uint32_t k = (uint32_t)((cnt - 1) / 2);  // a box holds fewer than 2^32 voxels
   uint32_t d, cum, bucket;
-  if (!block_select_small(lds, kBins1, k, sh, &d, &cum, &bucket)) {
+  if (!block_select_small(lds, kBins1, k, sh, &d, &cum, &bucket, [](uint32_t i) { return digit_slot<DT>(i); })) {
     if (t == 0) {
       R.status = TSA_EDEVICE;
       s.finished = 1;
@@ -681,13 +656,14 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
   uint32_t* l2 = lds + hsize;
   lds_zero(lds, hsize + kBins2);
   __syncthreads();
-  BPass2<DT> f2{HistOwnAcc{lds, lo, scale, a.nbins - 1, a.rshift, (uint32_t)t & ((1u << a.rshift) - 1u)},
-                Level2Acc<DT>{l2, prefix >> kShift1, compact, cand_sink(cs, a.pool + cand_base, &s.cand_fill, bucket)},
-                VarAcc{shift}, hist_on, var_on};
+  Pass2Acc<DT, HistOwnAcc> f2{
+      HistOwnAcc(lds, lo, scale, a.nbins, a.rshift),
+      Level2Acc<DT>(l2, prefix, true, compact, cand_sink(cs, a.pool + cand_base, &s.cand_fill, bucket)),
+      VarAcc{shift}, hist_on, true, var_on};
   walk_tile<DT, VEC, NT>(a, g, 0u, f2);
   f2.l2.finish();
   __syncthreads();
-  if (hist_on) lds_flush(lds, (uint32_t)a.nbins, a.rshift, a.hists + (size_t)q * a.nbins);
+  if (hist_on) lds_flush_hist(lds, (uint32_t)a.nbins, a.rshift, a.hists + (size_t)q * a.nbins);
   if (var_on) {
     const double vq = wave_sum_f64(f2.var.q);
     const int w = t / kWave, lane = t % kWave;
@@ -751,7 +727,7 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
 // ---------------------------------------------------------------------------
 // the persistent kernel
 // ---------------------------------------------------------------------------
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   __shared__ BShared sh;
@@ -797,7 +773,7 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
     if (phase == 1) {
       lds_zero(lds, kBins1 + kTrash);
       __syncthreads();
-      BPass1<DT> f{MomAcc<DT, false>{}, Digit1Acc<DT>{lds, 0u, 0u}};
+      Pass1Acc<DT> f(lds, 0u);
       walk_tile<DT, VEC, NT>(a, g, tile, f);
       __syncthreads();
       uint32_t c = 0;  // every valid value incremented one first-digit counter
@@ -807,7 +783,7 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
       __syncthreads();
       uint32_t* dig = a.digits + (size_t)q * kBins1;
       for (int b = t; b < kBins1; b += kBBlock) {
-        const uint32_t c = lds[b];
+        const uint32_t c = lds[digit_slot<DT>(b)];
         if (c) atomicAdd(dig + b, c);
       }
     } else if (phase == 2) {
@@ -818,14 +794,14 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
         lds_zero(lds, hsize + kBins2);
         __syncthreads();
         const bool hist_on = s.hist_ok != 0, var_on = DT == 0 && s.var_on != 0;
-        BPass2<DT> f{HistOwnAcc{lds, s.lo, s.scale, a.nbins - 1, a.rshift, (uint32_t)t & ((1u << a.rshift) - 1u)},
-                     Level2Acc<DT>{l2, s.prefix >> kShift1, s.compact != 0,
-                                   cand_sink(cs, a.pool + s.cand_base, &s.cand_fill, s.cand_n)},
-                     VarAcc{s.shift}, hist_on, var_on};
+        Pass2Acc<DT, HistOwnAcc> f{
+            HistOwnAcc(lds, s.lo, s.scale, a.nbins, a.rshift),
+            Level2Acc<DT>(l2, s.prefix, true, s.compact != 0, cand_sink(cs, a.pool + s.cand_base, &s.cand_fill, s.cand_n)),
+            VarAcc{s.shift}, hist_on, true, var_on};
         walk_tile<DT, VEC, NT>(a, g, tile, f);
         f.l2.finish();
         __syncthreads();
-        if (hist_on) lds_flush(lds, (uint32_t)a.nbins, a.rshift, a.hists + (size_t)q * a.nbins);
+        if (hist_on) lds_flush_hist(lds, (uint32_t)a.nbins, a.rshift, a.hists + (size_t)q * a.nbins);
         uint32_t* dig = a.digits + (size_t)q * kBins1;
         for (int b = t; b < kBins2; b += kBBlock) {
           const uint32_t c = l2[b];
@@ -1150,7 +1126,7 @@ static int enqueue_region_batch(const tsa_cube* cube, const tsa_region* d_region
   }
   if (tile_units && tile_units < 256) tile_units = 256;
   const int epv = cube->dtype == TSA_F32 ? 4 : 8;
-  const bool vec = ((uintptr_t)cube->data % 16) == 0 && (cube->nx % epv) == 0;
+  const int vec = row_mode(cube);
   if (!vec) tile_units *= (uint32_t)epv;  // scalar units are elements
   char* ws = (char*)d_ws;
   BArgs a;
@@ -1172,7 +1148,7 @@ static int enqueue_region_batch(const tsa_cube* cube, const tsa_region* d_region
   a.max_tiles = L.max_tiles;
   a.cand_max = cand_max;
   a.pool_keys = L.pool_keys;
-  a.vec = vec ? 1 : 0;
+  a.vec = vec;
   a.results = d_results;
   a.hists = d_hists;
   a.hdr = (BatchHdr*)(ws + L.hdr);
@@ -1202,17 +1178,24 @@ static int enqueue_region_batch(const tsa_cube* cube, const tsa_region* d_region
     TSA_TRACED("batch_plan", s, hipLaunchKernelGGL(k_bplan<1>, dim3(pb), dim3(256), 0, s, a));
   TSA_TRACED("batch_scan", s, hipLaunchKernelGGL(k_bscan, dim3(1), dim3(1024), 0, s, a));
   const int grid = (int)a.grid;
+#define TSA_BATCH_LAUNCH(D, V, N) \
+  TSA_TRACED("batch", s, hipLaunchKernelGGL((k_batch<D, V, N>), dim3(grid), dim3(kBBlock), lds, s, a))
   if (cube->dtype == TSA_F32) {
-    if (vec)
-      TSA_TRACED("batch", s, hipLaunchKernelGGL((k_batch<0, true, true>), dim3(grid), dim3(kBBlock), lds, s, a));
+    if (vec == 1)
+      TSA_BATCH_LAUNCH(0, 1, true);
+    else if (vec == 2)
+      TSA_BATCH_LAUNCH(0, 2, true);
     else
-      TSA_TRACED("batch", s, hipLaunchKernelGGL((k_batch<0, false, false>), dim3(grid), dim3(kBBlock), lds, s, a));
+      TSA_BATCH_LAUNCH(0, 0, false);
   } else {
-    if (vec)
-      TSA_TRACED("batch", s, hipLaunchKernelGGL((k_batch<1, true, true>), dim3(grid), dim3(kBBlock), lds, s, a));
+    if (vec == 1)
+      TSA_BATCH_LAUNCH(1, 1, true);
+    else if (vec == 2)
+      TSA_BATCH_LAUNCH(1, 2, true);
     else
-      TSA_TRACED("batch", s, hipLaunchKernelGGL((k_batch<1, false, false>), dim3(grid), dim3(kBBlock), lds, s, a));
+      TSA_BATCH_LAUNCH(1, 0, false);
   }
+#undef TSA_BATCH_LAUNCH
   TSA_TRACED("batch_final", s, hipLaunchKernelGGL(k_bfinal, dim3(pb), dim3(256), 0, s, a));
   return hipGetLastError() == hipSuccess ? TSA_OK : TSA_EDEVICE;
 }

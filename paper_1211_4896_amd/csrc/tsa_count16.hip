@@ -29,10 +29,9 @@ constexpr uint32_t kGroup = 1024, kGroups = kVals / kGroup;
 constexpr int kCountThreads = 1024;
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
 
 TSA_DEV uint32_t lds_add_rtn(uint32_t byte_addr, uint32_t v) {
-  return __hip_atomic_fetch_add((lds_u32*)(uintptr_t)byte_addr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return __hip_atomic_fetch_add((lds_word*)(uintptr_t)byte_addr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 TSA_DEV uint32_t pk_max(uint32_t a, uint32_t b) {
   const u16x2 m = __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b));
@@ -85,14 +84,14 @@ struct Count16Acc {
 
 // tables: one table of kWords per block; else (null) the counts are added to
 // pk, word i as (low half, high half) of one 64-bit counter.
-template <bool VEC>
+template <int VEC>
 __global__ __launch_bounds__(kCountThreads) void k_count16(Geom g, uint32_t* __restrict__ tables,
                                                            uint64_t* __restrict__ pk, uint64_t* __restrict__ adj) {
   __shared__ __align__(16) uint32_t lds[kWords];
   for (uint32_t i = threadIdx.x; i < kWords / 4; i += blockDim.x) ((uint4*)lds)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  Count16Acc a{(uint32_t)(uintptr_t)(lds_u32*)lds, adj};
-  walk_stream<1, VEC, kUnroll, true>(g, a);
+  Count16Acc a{lds_byte_addr(lds), adj};
+  walk<1, VEC, kUnroll, true, true>(g, a);
   __syncthreads();
   if (tables) {
     uint4* t = (uint4*)(tables + (size_t)blockIdx.x * kWords);
@@ -388,7 +387,7 @@ int count16_mode(int64_t volume, int grid, size_t table_bytes, const Count16Ask&
   return volume < (1ll << 32) ? 2 : 0;
 }
 
-int run_count16(const Geom& g, bool vec, int grid, int mode, void* scratch, void* small, void* tables,
+int run_count16(const Geom& g, int vec, int grid, int mode, void* scratch, void* small, void* tables,
                 const Count16Ask& ask, hipStream_t s) {
   uint64_t* adj = (uint64_t*)scratch;
   uint64_t* pk = adj + kVals;
@@ -397,12 +396,15 @@ int run_count16(const Geom& g, bool vec, int grid, int mode, void* scratch, void
   uint32_t* tab = mode == 1 ? (uint32_t*)tables : nullptr;
   const uint32_t clear = mode == 1 ? kVals : kVals + kWords;
   TSA_TRACED("clear16", s, hipLaunchKernelGGL(k_clear16, dim3((clear + 255) / 256), dim3(256), 0, s, adj, clear));
-  if (vec)
-    TSA_TRACED("count16", s,
-               hipLaunchKernelGGL(k_count16<true>, dim3(grid), dim3(kCountThreads), 0, s, g, tab, pk, adj));
+#define TSA_COUNT16(V) \
+  TSA_TRACED("count16", s, hipLaunchKernelGGL(k_count16<V>, dim3(grid), dim3(kCountThreads), 0, s, g, tab, pk, adj))
+  if (vec == 1)
+    TSA_COUNT16(1);
+  else if (vec == 2)
+    TSA_COUNT16(2);
   else
-    TSA_TRACED("count16", s,
-               hipLaunchKernelGGL(k_count16<false>, dim3(grid), dim3(kCountThreads), 0, s, g, tab, pk, adj));
+    TSA_COUNT16(0);
+#undef TSA_COUNT16
   TSA_TRACED("reduce16", s,
              hipLaunchKernelGGL(k_reduce16, dim3(kGroups), dim3(kGroup), 0, s, (const uint32_t*)tab, grid,
                                 (const uint64_t*)pk, adj, groups));

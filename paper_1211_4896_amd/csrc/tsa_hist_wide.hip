@@ -11,7 +11,7 @@
 
 namespace tsa {
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_hist16(Geom g, float lo, float hi, float scale, int32_t nbins, int32_t b0,
                                                  int32_t nb, uint32_t epoch, uint64_t* __restrict__ counts,
                                                  uint64_t* __restrict__ outl, int count_out) {
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(1024) void k_hist16(Geom g, float lo, float hi, flo
   if (count_out) block_add_outliers(h.below, h.above, outl, osm);
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 static int launch_hist16(const Geom& g, int grid, int block, size_t lds, float lo, float hi, float scale,
                          int32_t nbins, int32_t b0, int32_t nb, uint32_t epoch, uint64_t* counts, uint64_t* outl,
                          int count_out, hipStream_t s) {
@@ -40,7 +40,7 @@ static int launch_hist16(const Geom& g, int grid, int block, size_t lds, float l
   return hipGetLastError() == hipSuccess ? TSA_OK : TSA_EDEVICE;
 }
 
-int run_histogram_wide(const tsa_cube* cube, const Geom& g, bool vec, int grid, int block, float lo, float hi,
+int run_histogram_wide(const tsa_cube* cube, const Geom& g, int vec, int grid, int block, float lo, float hi,
                        float scale, int32_t nbins, uint64_t* d_counts, uint64_t* d_outl, hipStream_t s) {
   DevInfo dev;
   int st = device_info(&dev);
@@ -54,23 +54,17 @@ int run_histogram_wide(const tsa_cube* cube, const Geom& g, bool vec, int grid, 
   int64_t ep = (65535 - 16) / per_chunk;
   if (ep < 1) return TSA_ENOTSUP;
   const uint32_t epoch = (uint32_t)ep;
-  const bool nt = true;
   for (int32_t b0 = 0; b0 < nbins; b0 += per_pass) {
     const int32_t nb = (nbins - b0) < per_pass ? (nbins - b0) : per_pass;
     const size_t lds = (size_t)((nb + 1) / 2) * 4;
     const int co = b0 == 0;
-    if (cube->dtype == TSA_F32) {
-      st = vec ? launch_hist16<0, true, true>(g, grid, block, lds, lo, hi, scale, nbins, b0, nb, epoch, d_counts,
-                                              d_outl, co, s)
-               : launch_hist16<0, false, false>(g, grid, block, lds, lo, hi, scale, nbins, b0, nb, epoch, d_counts,
-                                                d_outl, co, s);
-    } else {
-      st = vec ? launch_hist16<1, true, true>(g, grid, block, lds, lo, hi, scale, nbins, b0, nb, epoch, d_counts,
-                                              d_outl, co, s)
-               : launch_hist16<1, false, false>(g, grid, block, lds, lo, hi, scale, nbins, b0, nb, epoch, d_counts,
-                                                d_outl, co, s);
-    }
-    (void)nt;
+#define TSA_HIST16(D, V, N) \
+  launch_hist16<D, V, N>(g, grid, block, lds, lo, hi, scale, nbins, b0, nb, epoch, d_counts, d_outl, co, s)
+    if (cube->dtype == TSA_F32)
+      st = vec == 1 ? TSA_HIST16(0, 1, true) : vec == 2 ? TSA_HIST16(0, 2, true) : TSA_HIST16(0, 0, false);
+    else
+      st = vec == 1 ? TSA_HIST16(1, 1, true) : vec == 2 ? TSA_HIST16(1, 2, true) : TSA_HIST16(1, 0, false);
+#undef TSA_HIST16
     if (st) return st;
   }
   return TSA_OK;

@@ -16,7 +16,7 @@
 namespace tsa {
 
 constexpr int kUnroll = 4;            // 16-byte loads in flight per lane
-constexpr uint32_t kTileUnits = 8192; // vectors per rows tile (single-region calls)
+constexpr uint32_t kTileUnits = 8192; // vectors per rows tile (single-region calls), at most
 constexpr int kMaxBlocks = 7936;      // upper bound of a pass grid (moment partial slots)
 // The fused passes add their per-block counts into kHistCopies copies of a
 // histogram (block b into copy b % kHistCopies), summed by the next one-block
@@ -68,7 +68,9 @@ int graph_run(const GraphKey& key, hipStream_t s, int (*enqueue)(void* ctx, hipS
 Magic make_magic(uint32_t d);
 int check_cube(const tsa_cube* c);
 int region_box(const tsa_cube* c, const tsa_region* r, tsa_region* b);
-int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom* g, bool* vec, int64_t* volume);
+int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom* g, int* vec, int64_t* volume);
+// How the rows of boxes inside the cube are read (the walkers' VEC).
+int row_mode(const tsa_cube* c);
 size_t single_ws_bytes(int64_t volume);
 
 // int16 regions answered from the counts of their values (tsa_count16.hip):
@@ -87,14 +89,14 @@ size_t count16_scratch_bytes();
 size_t count16_small_bytes();
 int count16_grid(int64_t volume, int blocks);
 int count16_mode(int64_t volume, int grid, size_t table_bytes, const Count16Ask& ask);
-int run_count16(const Geom& g, bool vec, int grid, int mode, void* scratch, void* small, void* tables,
+int run_count16(const Geom& g, int vec, int grid, int mode, void* scratch, void* small, void* tables,
                 const Count16Ask& ask, hipStream_t s);
 
 int run_moments(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out, void* d_ws, size_t ws_bytes,
                 tsa_stream_t stream);
 int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, float hi, int32_t nbins,
                   uint64_t* d_counts, uint64_t* d_outliers, void* d_ws, size_t ws_bytes, tsa_stream_t stream);
-int run_histogram_wide(const tsa_cube* cube, const Geom& g, bool vec, int grid, int block, float lo, float hi,
+int run_histogram_wide(const tsa_cube* cube, const Geom& g, int vec, int grid, int block, float lo, float hi,
                        float scale, int32_t nbins, uint64_t* d_counts, uint64_t* d_outl, hipStream_t s);
 int run_median(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out, void* d_ws, size_t ws_bytes,
                tsa_stream_t stream);

@@ -40,7 +40,7 @@ __global__ void k_fill_set(FillSet f) {
 // ---------------------------------------------------------------------------
 // float32 lanes sum about a shift of their own and the partials hold
 // (n, mean, M2); int16 partials hold exact integer sums.
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_moments(Geom g, Partial* __restrict__ parts) {
   __shared__ MomShared sm;
   if constexpr (DT == 0) {
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(1024) void k_moments(Geom g, Partial* __restrict__ 
 // ---------------------------------------------------------------------------
 // fixed-range histogram pass (Section 4.1)
 // ---------------------------------------------------------------------------
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_hist(Geom g, float lo, float hi, float scale, int32_t nbins,
                                                uint32_t rshift, uint64_t* __restrict__ counts,
                                                uint64_t* __restrict__ outl) {
@@ -65,10 +65,10 @@ __global__ __launch_bounds__(1024) void k_hist(Geom g, float lo, float hi, float
   __shared__ uint32_t osm[32];
   lds_zero(lds, ((uint32_t)nbins << rshift) + kTrash);
   __syncthreads();
-  HistAcc h{lds, lo, hi, scale, nbins - 1, rshift, threadIdx.x & ((1u << rshift) - 1u)};
+  HistAcc<DT> h(lds, lo, hi, scale, nbins, rshift);
   walk<DT, VEC, kUnroll, NT>(g, h);
   __syncthreads();
-  lds_flush(lds, (uint32_t)nbins, rshift, counts);
+  lds_flush_hist(lds, (uint32_t)nbins, rshift, counts);
   block_add_outliers(h.below, h.above, outl, osm);
 }
 
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_hist_place(const void* base, 
   }
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_hist_win(Geom g, float lo, float hi, float scale, int32_t nbins,
                                                    const int32_t* __restrict__ w0p, uint64_t* __restrict__ counts,
                                                    uint64_t* __restrict__ outl) {
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(1024) void k_hist_win(Geom g, float lo, float hi, f
   const int32_t w0 = *w0p;
   lds_zero(lds, kWinBins);
   __syncthreads();
-  HistWinOutAcc h{lds, lo, hi, scale, nbins - 1, w0, counts};
+  HistWinOutAcc<DT> h{lds, lo, hi, scale, nbins - 1, w0, counts};
   walk<DT, VEC, kUnroll, NT>(g, h);
   __syncthreads();
   const uint32_t nw = (uint32_t)min((int32_t)kWinBins, nbins - w0);
@@ -296,20 +296,20 @@ TSA_DEV void select_tail(int level, const uint64_t* hist, SelState* st, const Ta
 // ---------------------------------------------------------------------------
 // radix selection: level passes over the cube
 // ---------------------------------------------------------------------------
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_level1(Geom g, uint32_t rshift, SelState* __restrict__ st,
                                                  uint64_t* __restrict__ hist1, Tail tl) {
   extern __shared__ uint32_t lds[];
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
-  Digit1Acc<DT> d{lds, rshift, threadIdx.x & ((1u << rshift) - 1u)};
+  Digit1Acc<DT> d(lds, rshift);
   walk<DT, VEC, kUnroll, NT>(g, d);
   __syncthreads();
-  lds_flush(lds, kBins1, rshift, hist1);
+  lds_flush_digits<DT>(lds, rshift, hist1);
   select_tail(1, hist1, st, tl);
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_level2(Geom g, SelState* __restrict__ st, uint64_t* __restrict__ hist2,
                                                  uint32_t* __restrict__ cand, Tail tl) {
   __shared__ uint32_t lds[kBins2];
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(1024) void k_level2(Geom g, SelState* __restrict__ 
   if (st->done) return;
   lds_zero(lds, kBins2);
   __syncthreads();
-  Level2Acc<DT> a{lds, st->prefix >> kShift1, st->compact != 0, cand_sink(cs, cand, &st->ncand, st->cand_cap)};
+  Level2Acc<DT> a(lds, st->prefix, true, st->compact != 0, cand_sink(cs, cand, &st->ncand, st->cand_cap));
   walk<DT, VEC, kUnroll, NT>(g, a);
   a.finish();
   __syncthreads();
@@ -334,7 +334,7 @@ struct HistCopies {
   uint64_t* counts;
   int32_t nbins;
 };
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_level3(Geom g, SelState* __restrict__ st, uint64_t* __restrict__ hist3,
                                                  const uint32_t* __restrict__ cand, int first, Tail tl,
                                                  HistCopies hc) {
@@ -491,7 +491,7 @@ TSA_DEV void median_of_state(const SelState* med, float& mf, int32_t& mi) {
   mi = i16_of_key(k);
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_mlevel1(Geom g, uint32_t rshift, const SelState* __restrict__ med,
                                                   SelState* __restrict__ st, uint64_t* __restrict__ hist1, Tail tl) {
   extern __shared__ uint32_t lds[];
@@ -501,14 +501,14 @@ __global__ __launch_bounds__(1024) void k_mlevel1(Geom g, uint32_t rshift, const
   float mf;
   int32_t mi;
   median_of_state<DT>(med, mf, mi);
-  AbsDev<DT, Digit1Acc<0>> a{Digit1Acc<0>{lds, rshift, threadIdx.x & ((1u << rshift) - 1u)}, mf, mi};
+  AbsDev<DT, Digit1Acc<0>> a{Digit1Acc<0>(lds, rshift), mf, mi};
   walk<DT, VEC, kUnroll, NT>(g, a);
   __syncthreads();
-  lds_flush(lds, kBins1, rshift, hist1);
+  lds_flush_digits<0>(lds, rshift, hist1);
   select_tail(1, hist1, st, tl);
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_mlevel2(Geom g, const SelState* __restrict__ med, SelState* __restrict__ st,
                                                   uint64_t* __restrict__ hist2, uint32_t* __restrict__ cand, Tail tl) {
   __shared__ uint32_t lds[kBins2];
@@ -520,8 +520,7 @@ __global__ __launch_bounds__(1024) void k_mlevel2(Geom g, const SelState* __rest
   int32_t mi;
   median_of_state<DT>(med, mf, mi);
   AbsDev<DT, Level2Acc<0>> a{
-      Level2Acc<0>{lds, st->prefix >> kShift1, st->compact != 0, cand_sink(cs, cand, &st->ncand, st->cand_cap)}, mf,
-      mi};
+      Level2Acc<0>(lds, st->prefix, true, st->compact != 0, cand_sink(cs, cand, &st->ncand, st->cand_cap)), mf, mi};
   walk<DT, VEC, kUnroll, NT>(g, a);
   a.inner.finish();
   __syncthreads();
@@ -541,7 +540,7 @@ TSA_DEV void mad_finish(const SelState* med, const SelState* st, int dtype, doub
   out[2] = (double)med->n;
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_mlevel3(Geom g, const SelState* __restrict__ med, SelState* __restrict__ st,
                                                   uint64_t* __restrict__ hist3, const uint32_t* __restrict__ cand,
                                                   Tail tl, int med_dtype, double* __restrict__ out) {
@@ -579,18 +578,6 @@ __global__ __launch_bounds__(1024) void k_mlevel3(Geom g, const SelState* __rest
 // fused trio: pass A (moments + digit 1), mid (merge + select 1 + range),
 // pass B (histogram over [min, max] + level 2)
 // ---------------------------------------------------------------------------
-template <int DT>
-struct PassA {
-  MomAcc<DT, false> mom;  // the count is the digit histogram's total
-  Digit1Acc<DT> d1;
-  template <class T>
-  TSA_DEV void operator()(T raw, bool in) {
-    mom(raw, in);
-    d1(raw, in);
-  }
-  TSA_DEV void chunk() {}
-};
-
 // Pass A's last block: merges the moments, fixes the histogram's range and the
 // shift of the second moment, and chooses the first digit.  lds: 8 kBins1
 // bytes and 32 a thread (the larger).
@@ -666,11 +653,9 @@ TSA_DEV void mid_tail(const Partial* parts, int np, int dtype, uint64_t volume, 
   }
 }
 
-// The loads run a chunk ahead (walk_stream): 1024x1024x1280 voxels (5.4 GB)
-// 0.85 -> 0.83 ms, 6.4 TB/s.  Pass B loses by it (0.96 -> 1.15 ms: the second
-// set of vectors costs it a block per compute unit); the histogram, moments
-// and level passes gain nothing.
-template <int DT, bool VEC, bool NT>
+// Bound by HBM: 1024x1024x1280 voxels (5.4 GB) 0.90 ms, 6.0 TB/s (0.91 without
+// the loads a chunk ahead; the same launch with only the loads takes 0.86).
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_a(Geom g, uint32_t rshift, Partial* __restrict__ parts,
                                                  uint64_t* __restrict__ hist1, uint64_t* __restrict__ hcopy,
                                                  uint32_t hcopy_n, SelState* __restrict__ st,
@@ -683,8 +668,8 @@ __global__ __launch_bounds__(1024) void k_pass_a(Geom g, uint32_t rshift, Partia
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < hcopy_n; i += gridDim.x * blockDim.x) hcopy[i] = 0ull;
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
-  PassA<DT> a{MomAcc<DT, false>{}, Digit1Acc<DT>{lds, rshift, threadIdx.x & ((1u << rshift) - 1u)}};
-  walk_stream<DT, VEC, kUnroll, NT>(g, a);
+  Pass1Acc<DT> a(lds, rshift);
+  walk<DT, VEC, kUnroll, NT, DT == 0>(g, a);
   // every valid value incremented one first-digit counter: the block's count
   // is their total (each lane adds a strided share; the partial sums them)
   __syncthreads();
@@ -694,27 +679,10 @@ __global__ __launch_bounds__(1024) void k_pass_a(Geom g, uint32_t rshift, Partia
   block_store_partial(a.mom, sm, &sm_part);  // thread 0's
   if (threadIdx.x == 0) publish_partial(sm_part, parts + blockIdx.x);
   __syncthreads();
-  lds_flush(lds, kBins1, rshift, hist1 + (size_t)(blockIdx.x % kHistCopies) * kBins1);
+  lds_flush_digits<DT>(lds, rshift, hist1 + (size_t)(blockIdx.x % kHistCopies) * kBins1);
   if (last_block(arrive))
     mid_tail(parts, (int)gridDim.x, DT, volume, nbins, hist1, st, out, (uint64_t*)lds);
 }
-
-template <int DT>
-struct PassB {
-  HistOwnAcc h;
-  Level2Acc<DT> l2;
-  VarAcc var;
-  bool hist_on, var_on;
-  template <class T>
-  TSA_DEV void operator()(T raw, bool in) {
-    if (hist_on) h(raw, in);
-    l2(raw, in);
-    if constexpr (DT == 0) {
-      if (var_on) var(raw, in);
-    }
-  }
-  TSA_DEV void chunk() {}
-};
 
 // Pass B's last block: M2 about the shift c, M2 = sum (x-c)^2 - n (mean - c)^2,
 // the block partials added in a fixed order (strided per thread, then a
@@ -745,7 +713,7 @@ TSA_DEV void pass_b_tail(const Partial* parts2, SelState* st, const uint64_t* hi
   select_level(2, hist2, st, tl.dtype, tl.volume, tl.out, false, ssm);
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t rshift, uint32_t stage,
                                                  SelState* __restrict__ st,
                                                  uint64_t* __restrict__ counts, uint64_t* __restrict__ outl,
@@ -766,14 +734,15 @@ __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t
   lds_zero(lds, hsize + kBins2);
   const CandSink sink = cand_sink_lds(l2 + kBins2, stage, cand, &st->ncand, st->cand_cap);
   __syncthreads();
-  PassB<DT> b{HistOwnAcc{lds, st->lo, st->scale, nbins - 1, rshift, threadIdx.x & ((1u << rshift) - 1u)},
-              Level2Acc<DT>{l2, sel_on ? (st->prefix >> kShift1) : 0xFFFFFFFFu, sel_on && st->compact != 0, sink},
-              VarAcc{st->shift}, hist_on, var_on};
+  Pass2Acc<DT, HistOwnAcc> b{HistOwnAcc(lds, st->lo, st->scale, nbins, rshift),
+                             Level2Acc<DT>(l2, st->prefix, sel_on, st->compact != 0, sink), VarAcc{st->shift},
+                             hist_on, sel_on, var_on};
   walk<DT, VEC, kUnroll, NT>(g, b);
   b.l2.finish();
   __syncthreads();
   // into one of kHistCopies copies (counts holds them nbins apart), summed by k_level3
-  if (hist_on) lds_flush(lds, (uint32_t)nbins, rshift, counts + (size_t)(blockIdx.x % kHistCopies) * (uint32_t)nbins);
+  if (hist_on)
+    lds_flush_hist(lds, (uint32_t)nbins, rshift, counts + (size_t)(blockIdx.x % kHistCopies) * (uint32_t)nbins);
   if (sel_on) lds_flush(l2, kBins2, 0, hist2);
   // values lie in their own [min, max]: the outlier counters keep their zeros
   if (var_on) {
@@ -786,24 +755,7 @@ __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t
 // Pass B with a window of kWinBins 32-bit LDS counters (more bins than fit):
 // one 1024-lane block per compute unit; values outside the window go straight
 // to the global bins.
-template <int DT>
-struct PassBWin {
-  HistWinAcc h;
-  Level2Acc<DT> l2;
-  VarAcc var;
-  bool hist_on, var_on;
-  template <class T>
-  TSA_DEV void operator()(T raw, bool in) {
-    if (hist_on) h(raw, in);
-    l2(raw, in);
-    if constexpr (DT == 0) {
-      if (var_on) var(raw, in);
-    }
-  }
-  TSA_DEV void chunk() {}
-};
-
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_bwin(Geom g, int32_t nbins, SelState* __restrict__ st,
                                                     uint64_t* __restrict__ counts, uint64_t* __restrict__ hist2,
                                                     uint32_t* __restrict__ cand, Partial* __restrict__ parts2,
@@ -821,9 +773,9 @@ __global__ __launch_bounds__(1024) void k_pass_bwin(Geom g, int32_t nbins, SelSt
   const CandSink sink = cand_sink_lds(l2 + kBins2, kWaveStage, cand, &st->ncand, st->cand_cap);
   __syncthreads();
   const int32_t w0 = st->win0;
-  PassBWin<DT> b{HistWinAcc{lds, st->lo, st->scale, nbins - 1, w0, counts},
-                 Level2Acc<DT>{l2, sel_on ? (st->prefix >> kShift1) : 0xFFFFFFFFu, sel_on && st->compact != 0, sink},
-                 VarAcc{st->shift}, hist_on, var_on};
+  Pass2Acc<DT, HistWinAcc> b{HistWinAcc{lds, st->lo, st->scale, nbins - 1, w0, counts},
+                             Level2Acc<DT>(l2, st->prefix, sel_on, st->compact != 0, sink), VarAcc{st->shift},
+                             hist_on, sel_on, var_on};
   walk<DT, VEC, kUnroll, NT>(g, b);
   b.l2.finish();
   __syncthreads();
@@ -863,7 +815,7 @@ struct PassB16 {
   }
 };
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_b16(Geom g, int32_t nbins, uint32_t epoch, SelState* __restrict__ st,
                                                    uint64_t* __restrict__ counts, uint64_t* __restrict__ outl,
                                                    uint64_t* __restrict__ hist2, uint32_t* __restrict__ cand,
@@ -882,8 +834,8 @@ __global__ __launch_bounds__(1024) void k_pass_b16(Geom g, int32_t nbins, uint32
   lds_zero(lds, hwords + kBins2);
   __syncthreads();
   PassB16<DT> b{Hist16Acc{lds, st->lo, st->hi, st->scale, nbins - 1, 0, nbins, counts, epoch, 0u, true, 0u, 0u},
-                Level2Acc<DT>{l2, sel_on ? (st->prefix >> kShift1) : 0xFFFFFFFFu, sel_on && st->compact != 0,
-                              cand_sink(cs, cand, &st->ncand, st->cand_cap)},
+                Level2Acc<DT>(l2, st->prefix, sel_on, st->compact != 0,
+                              cand_sink(cs, cand, &st->ncand, st->cand_cap)),
                 VarAcc{st->shift}, hist_on, var_on};
   walk<DT, VEC, kUnroll, NT>(g, b);
   b.l2.finish();
@@ -969,22 +921,39 @@ int region_box(const tsa_cube* c, const tsa_region* r, tsa_region* b) {
   return TSA_OK;
 }
 
+int row_mode(const tsa_cube* c) {
+  const int64_t esz = c->dtype == TSA_F32 ? 4 : 2;
+  if ((uintptr_t)c->data % esz) return 0;
+  return (uintptr_t)c->data % 16 == 0 && c->nx % (16 / esz) == 0 ? 1 : 2;
+}
+
 // Build the walk geometry of box b; tile_units = target vectors per rows tile.
-int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom* g, bool* vec, int64_t* volume) {
+// A box read at any element boundary is cut into about a thousand tiles, of
+// 8192 voxels at least (a 95x91x97 box: 26 tiles of 8192 vectors leave most of
+// the chip idle, 104 of 8192 voxels take half the time, and 400 of 512 vectors
+// spend longer adding their counters up than counting).
+int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom* g, int* vec, int64_t* volume) {
   const int64_t esz = c->dtype == TSA_F32 ? 4 : 2;
   const int64_t epv = 16 / esz;
   const int64_t lx = b.x1 - b.x0, ly = b.y1 - b.y0, lz = b.z1 - b.z0;
   *volume = lx * ly * lz;
   memset(g, 0, sizeof(*g));
   g->base = c->data;
-  const bool aligned = ((uintptr_t)c->data % 16) == 0;
-  const int64_t e0 = b.x0 + c->nx * (b.y0 + c->ny * b.z0);
+  int64_t e0 = b.x0 + c->nx * (b.y0 + c->ny * b.z0);
   const bool contig = (lx == c->nx && (ly == c->ny || lz == 1)) || (ly == 1 && lz == 1);
+  *vec = row_mode(c);
   if (contig) {
     g->mode = 0;
+    if (*vec) {
+      // vectors from the aligned address at or below the cube's; those that
+      // begin before the run are not visited
+      const int64_t mis = (int64_t)((uintptr_t)c->data % 16) / esz;
+      g->base = (const char*)c->data - mis * esz;
+      e0 += mis;
+      *vec = 1;
+    }
     const int64_t e1 = e0 + *volume;
-    *vec = aligned;
-    if (aligned) {
+    if (*vec) {
       int64_t v0 = (e0 + epv - 1) / epv, v1 = e1 / epv;
       if (v0 >= v1) {
         g->v0 = g->v1 = 0;
@@ -1009,8 +978,7 @@ int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom*
   if ((uint64_t)ly * (uint64_t)lz > 0xFFFFFFFFull) return TSA_EINVAL;
   g->nrows = (uint32_t)(ly * lz);
   g->ly = (uint32_t)ly;
-  *vec = aligned && (c->nx % epv) == 0;
-  if (*vec) {
+  if (*vec == 1) {
     const int64_t c0 = b.x0 / epv, c1 = (b.x1 + epv - 1) / epv;
     g->v_origin = (b.x0 / epv) + (c->nx / epv) * (b.y0 + c->ny * b.z0);
     g->v_ystride = c->nx / epv;
@@ -1022,9 +990,20 @@ int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom*
     g->v_origin = e0;
     g->v_ystride = c->nx;
     g->v_zstride = c->nx * c->ny;
-    g->vpr = (uint32_t)lx;
-    g->head_skip = 0;
-    g->last_valid = 1;
+    if (*vec == 2) {
+      g->vpr = (uint32_t)((lx + epv - 1) / epv);
+      g->head_skip = lx < epv ? 0u : (uint32_t)(g->vpr * epv - lx);
+      g->last_valid = (uint32_t)(lx < epv ? lx : epv);
+    } else {
+      g->vpr = (uint32_t)lx;
+      g->head_skip = 0;
+      g->last_valid = 1;
+    }
+  }
+  if (*vec == 2) {
+    const uint64_t share = (uint64_t)g->nrows * g->vpr / 1024;
+    const uint32_t least = tile_units / (uint32_t)epv;
+    if (tile_units > share) tile_units = share < least ? least : (uint32_t)share;
   }
   uint32_t rpt = tile_units / g->vpr;
   if (rpt < 1) rpt = 1;
@@ -1037,7 +1016,7 @@ int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom*
 }
 
 // Blocks for a pass over geometry g.
-static int pass_grid(const Geom& g, bool vec, int block, int maxblocks) {
+static int pass_grid(const Geom& g, int vec, int block, int maxblocks) {
   int64_t want;
   if (g.mode == 0)
     want = vec ? (g.v1 - g.v0 + (int64_t)block * kUnroll - 1) / ((int64_t)block * kUnroll)
@@ -1124,33 +1103,35 @@ static void fill_set(std::initializer_list<FillRange> ranges, hipStream_t s, Sel
   TSA_TRACED("fill", s, hipLaunchKernelGGL(k_fill_set, dim3(blocks), dim3(256), 0, s, f));
 }
 
-#define TSA_DISPATCH(DTV, VECV, NTV, EXPR)                              \
-  do {                                                                  \
-    if ((DTV) == 0 && (VECV) && (NTV)) {                                \
-      constexpr int DT = 0;                                             \
-      constexpr bool VEC = true, NT = true;                             \
-      EXPR;                                                             \
-    } else if ((DTV) == 0 && (VECV) && !(NTV)) {                        \
-      constexpr int DT = 0;                                             \
-      constexpr bool VEC = true, NT = false;                            \
-      EXPR;                                                             \
-    } else if ((DTV) == 0 && !(VECV)) {                                 \
-      constexpr int DT = 0;                                             \
-      constexpr bool VEC = false, NT = false;                           \
-      EXPR;                                                             \
-    } else if ((DTV) == 1 && (VECV) && (NTV)) {                         \
-      constexpr int DT = 1;                                             \
-      constexpr bool VEC = true, NT = true;                             \
-      EXPR;                                                             \
-    } else if ((DTV) == 1 && (VECV) && !(NTV)) {                        \
-      constexpr int DT = 1;                                             \
-      constexpr bool VEC = true, NT = false;                            \
-      EXPR;                                                             \
-    } else {                                                            \
-      constexpr int DT = 1;                                             \
-      constexpr bool VEC = false, NT = false;                           \
-      EXPR;                                                             \
-    }                                                                   \
+// The expression with the kernel's template constants: the type, how rows are read, and
+// whether loads are non-temporal (always for vectors at any element boundary).
+#define TSA_DISPATCH_AS(D, V, N, ...) \
+  {                                    \
+    constexpr int DT = D, VEC = V;     \
+    constexpr bool NT = N;             \
+    __VA_ARGS__;                       \
+  }
+#define TSA_DISPATCH(DTV, VECV, NTV, ...)       \
+  do {                                           \
+    if ((DTV) == 0) {                            \
+      if ((VECV) == 1 && (NTV))                  \
+        TSA_DISPATCH_AS(0, 1, true, __VA_ARGS__)        \
+      else if ((VECV) == 1)                      \
+        TSA_DISPATCH_AS(0, 1, false, __VA_ARGS__)       \
+      else if ((VECV) == 2)                      \
+        TSA_DISPATCH_AS(0, 2, true, __VA_ARGS__)        \
+      else                                       \
+        TSA_DISPATCH_AS(0, 0, false, __VA_ARGS__)       \
+    } else {                                     \
+      if ((VECV) == 1 && (NTV))                  \
+        TSA_DISPATCH_AS(1, 1, true, __VA_ARGS__)        \
+      else if ((VECV) == 1)                      \
+        TSA_DISPATCH_AS(1, 1, false, __VA_ARGS__)       \
+      else if ((VECV) == 2)                      \
+        TSA_DISPATCH_AS(1, 2, true, __VA_ARGS__)        \
+      else                                       \
+        TSA_DISPATCH_AS(1, 0, false, __VA_ARGS__)       \
+    }                                            \
   } while (0)
 
 // Common preparation of a single-region call.
@@ -1158,7 +1139,7 @@ struct Prep {
   DevInfo dev;
   tsa_region box;
   Geom g;
-  bool vec;
+  int vec;
   int64_t volume;
   WsLayout L;
   char* ws;
@@ -1166,13 +1147,17 @@ struct Prep {
   int block, grid, bpc;
 };
 
-// Blocks per compute unit by call (measured on the 1024x1024x1280 float32
-// cube): the fused trio and the moments gain from a third block per CU, the
-// histogram and the radix passes lose.
-constexpr int kBpcStats = 3, kBpcMoments = 3, kBpcHist = 2, kBpcSelect = 2;
+// Blocks per compute unit by call: the histogram and radix passes lose by a
+// third, the moments gain.  The fused trio takes three on large regions (pass A
+// and B on 1024x1024x1280 float32 voxels: 895 + 916 us, with two 865 + 933,
+// and the shorter lane sums carry less rounding) and where rows are read one by
+// one (1711x1711x246 box: 561 + 617 against 595 + 673), two below kTrio3 voxels,
+// where each has little to do (400^3: 104 us with two, 112 with three).
+constexpr int kBpcStats = 2, kBpcMoments = 3, kBpcHist = 2, kBpcSelect = 2;
+constexpr int64_t kTrio3 = 1ll << 28;
 
 static int prepare(const tsa_cube* cube, const tsa_region* region, void* d_ws, size_t ws_bytes,
-                   tsa_stream_t stream, Prep* P, int bpc_default, int64_t cand_limit = INT64_MAX) {
+                   tsa_stream_t stream, Prep* P, int bpc_default, int64_t cand_limit = INT64_MAX, bool trio = false) {
   int st = check_cube(cube);
   if (st) return st;
   if ((st = region_box(cube, region, &P->box))) return st;
@@ -1185,6 +1170,7 @@ static int prepare(const tsa_cube* cube, const tsa_region* region, void* d_ws, s
   const Tuning& T = tuning();
   P->block = T.block;
   P->bpc = T.bpc ? T.bpc : bpc_default;
+  if (!T.bpc && trio && (P->volume >= kTrio3 || P->g.mode == 1)) P->bpc = 3;
   int maxb = P->dev.cus * P->bpc;
   if (maxb > kMaxBlocks) maxb = kMaxBlocks;
   P->grid = pass_grid(P->g, P->vec, P->block, maxb);
@@ -1242,7 +1228,7 @@ static void reset_select(const Prep& P, const SelState& init, uint64_t* d_counts
            P.s, (SelState*)(P.ws + P.L.state), init);
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 static int launch_pass_b16(const Prep& P, int block, int grid, size_t lds, int32_t nbins, uint32_t epoch,
                            SelState* stp, uint64_t* d_counts, uint64_t* outl, uint64_t* h2, uint32_t* cand,
                            Partial* parts2, const Tail& tl) {
@@ -1255,7 +1241,7 @@ static int launch_pass_b16(const Prep& P, int block, int grid, size_t lds, int32
   return TSA_OK;
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 static int launch_pass_bwin(const Prep& P, int block, int grid, size_t lds, int32_t nbins, SelState* stp,
                             uint64_t* d_counts, uint64_t* h2, uint32_t* cand, Partial* parts2, const Tail& tl) {
   if (hipFuncSetAttribute((const void*)k_pass_bwin<DT, VEC, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1267,7 +1253,7 @@ static int launch_pass_bwin(const Prep& P, int block, int grid, size_t lds, int3
   return TSA_OK;
 }
 
-template <int DT, bool VEC, bool NT>
+template <int DT, int VEC, bool NT>
 static int launch_hist_win(const Prep& P, int grid, size_t lds, float lo, float hi, float scale, int32_t nbins,
                            const int32_t* w0p, uint64_t* d_counts, uint64_t* outl) {
   if (hipFuncSetAttribute((const void*)k_hist_win<DT, VEC, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1397,7 +1383,7 @@ int run_median(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out
 // ---------------------------------------------------------------------------
 struct Slab {
   Geom g;
-  bool vec;
+  int vec;
   int grid;
 };
 
@@ -1631,7 +1617,7 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
   if (!d_out || !d_counts) return TSA_EINVAL;
   if (nbins < 1 || nbins > 65536) return TSA_EINVAL;
   Prep P;
-  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcStats, cand_limit);
+  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcStats, cand_limit, true);
   if (st) return st;
   const size_t budget = P.dev.lds_per_block < 65536 ? P.dev.lds_per_block : 65536;
   const size_t cand_small = (size_t)(P.block / kWave) * kWaveStage * 4;  // pass B's candidate staging

@@ -289,23 +289,9 @@ constexpr uint32_t kMMCand = 4096;
 // counting ranks (no second-digit counters, no further block-wide scans).
 constexpr uint32_t kMMRankMax = 64;
 
-// LDS words by byte address.  The per-value increments add a shifted index to
-// a base held in a register (one shift-and-add), and add a register holding 1:
-// both values pass through an empty asm barrier so the compiler neither folds
-// the base back into a constant it adds separately nor rebuilds the 1 before
-// every increment.
-typedef __attribute__((address_space(3))) uint32_t lds_word;
-TSA_DEV uint32_t lds_byte_addr(uint32_t* p) { return (uint32_t)(uintptr_t)(lds_word*)p; }
-TSA_DEV uint32_t in_register(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
 TSA_DEV uint32_t in_scalar_register(uint32_t v) {
   asm volatile("" : "+s"(v));
   return v;
-}
-TSA_DEV void lds_add_at(uint32_t byte_addr, uint32_t v) {
-  __hip_atomic_fetch_add((lds_word*)(uintptr_t)byte_addr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 // A workgroup barrier that orders LDS only: this wave's LDS operations
 // complete, then the barrier.  __syncthreads() also waits for every global
@@ -430,8 +416,7 @@ __global__ __launch_bounds__(kMMBlock) __attribute__((amdgpu_waves_per_eu(EPT <=
         mom.s += d;
         mom.q = __builtin_fma(d, d, mom.q);
         const uint32_t k = key_f32(__float_as_uint(v));
-        mom.kmin = min(mom.kmin, k);
-        mom.kmax = max(mom.kmax, k);
+        mom.range.add(__float_as_uint(v));
         lds_add_at(dig_b + ((k >> kShift1) << word_shift), one);
       }
     }

@@ -2,17 +2,47 @@
 #pragma once
 
 #include <climits>
+#include <type_traits>
 
 #include "tsa_device.hpp"
 
-#ifndef TSA_BRANCHLESS
-#define TSA_BRANCHLESS 0
-#endif
-#ifndef TSA_BALLOT_COUNT
-#define TSA_BALLOT_COUNT 0
-#endif
-
 namespace tsa {
+
+// Accumulators take elements one at a time (operator(), masked by in_box and
+// the NaN test) and, where they have it, whole 16-byte vectors (vec).  vec
+// looks at its wave's values together first: where all are ordinary (no NaN,
+// in range), as nearly all are, no lane mask, select or branch is spent on a
+// single one; else the vector goes element by element.  The passes over the
+// data are bound by vector instructions as much as by HBM (15 a voxel kept
+// the SIMDs 70 % busy at 2 GHz), so vec is what sets their rate.
+
+// ---- LDS words by byte address ------------------------------------------------
+// The per-value increments add a shifted index to a base held in a register
+// (one shift-and-add), and add a register holding 1: both values pass through
+// an empty asm barrier so the compiler neither folds the base back into a
+// constant it adds separately nor rebuilds the 1 before every increment.
+typedef __attribute__((address_space(3))) uint32_t lds_word;
+TSA_DEV uint32_t lds_byte_addr(uint32_t* p) { return (uint32_t)(uintptr_t)(lds_word*)p; }
+TSA_DEV uint32_t in_register(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+TSA_DEV void lds_add_at(uint32_t byte_addr, uint32_t v) {
+  __hip_atomic_fetch_add((lds_word*)(uintptr_t)byte_addr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The four values of a float32 vector.
+struct Four {
+  uint32_t u[4];
+  float v[4];
+  TSA_DEV explicit Four(const uint4& r)
+      : u{r.x, r.y, r.z, r.w},
+        v{__uint_as_float(r.x), __uint_as_float(r.y), __uint_as_float(r.z), __uint_as_float(r.w)} {}
+  // whether some lane of the wave holds a NaN among its four (one compare tests two)
+  TSA_DEV bool wave_has_nan() const {
+    return __ballot(__builtin_isunordered(v[0], v[1]) || __builtin_isunordered(v[2], v[3])) != 0ull;
+  }
+};
 
 // ---- validity and key of one element ---------------------------------------
 template <int DT>
@@ -37,6 +67,28 @@ struct Elt<1> {
 template <int DT, bool COUNT = true>
 struct MomAcc;
 
+// totalOrder extremes of float32 bit patterns without forming keys: as signed
+// integers the non-negative values keep their order (hi), as unsigned ones the
+// negative values come above them, in reversed order (top, low).  One
+// three-operand instruction takes two values.
+struct RawRange {
+  int32_t hi = INT_MIN;
+  uint32_t top = 0u, low = 0xFFFFFFFFu;
+  TSA_DEV void add(uint32_t u) {
+    hi = max(hi, (int32_t)u);
+    top = max(top, u);
+    low = min(low, u);
+  }
+  TSA_DEV void add2(uint32_t a, uint32_t b) {
+    hi = max(max((int32_t)a, (int32_t)b), hi);
+    top = max(max(a, b), top);
+    low = min(min(a, b), low);
+  }
+  // keys of the smallest and largest value (0xFFFFFFFF and 0 when none was added)
+  TSA_DEV uint32_t kmin() const { return low > top ? 0xFFFFFFFFu : key_f32((top & 0x80000000u) ? top : low); }
+  TSA_DEV uint32_t kmax() const { return low > top ? 0u : key_f32(hi >= 0 ? (uint32_t)hi : low); }
+};
+
 // float32: per-lane running sums in double.  Each value and its square are
 // exact in double (a float32 square needs 48 significand bits and lies in
 // [2^-298, 2^256]), so every step rounds once, with relative error 2^-53.
@@ -46,23 +98,29 @@ struct MomAcc;
 template <bool COUNT>
 struct MomAcc<0, COUNT> {
   double s = 0.0, q = 0.0;
-  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u, cnt = 0u;
-  TSA_DEV void operator()(float x, bool in) {
-    const bool ok = Elt<0>::valid(x, in);
-    const double v = (double)(ok ? x : 0.0f);
+  RawRange range;
+  uint32_t cnt = 0u;
+  TSA_DEV void sums(float x) {
+    const double v = (double)x;
     s += v;
     q = __builtin_fma(v, v, q);
-    const uint32_t k = Elt<0>::key(x);
-    kmin = min(kmin, ok ? k : 0xFFFFFFFFu);
-    kmax = max(kmax, ok ? k : 0u);
-    if constexpr (COUNT) {
-#if TSA_BALLOT_COUNT
-      cnt += (uint32_t)__popcll(__ballot(ok));  // wave total, kept uniform (scalar unit)
-#else
-      cnt += ok ? 1u : 0u;
-#endif
+  }
+  TSA_DEV void operator()(float x, bool in) {
+    if (Elt<0>::valid(x, in)) {
+      sums(x);
+      range.add(__float_as_uint(x));
+      if constexpr (COUNT) ++cnt;
     }
   }
+  TSA_DEV void four(const Four& f) {  // none of them NaN
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sums(f.v[e]);
+    range.add2(f.u[0], f.u[1]);
+    range.add2(f.u[2], f.u[3]);
+    if constexpr (COUNT) cnt += 4u;
+  }
+  TSA_DEV uint32_t kmin() const { return range.kmin(); }
+  TSA_DEV uint32_t kmax() const { return range.kmax(); }
   TSA_DEV void chunk() {}
 };
 
@@ -71,16 +129,18 @@ template <bool COUNT>
 struct MomAcc<1, COUNT> {
   int64_t s = 0;
   uint64_t q = 0;
-  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u, cnt = 0u;
+  uint32_t mn = 0xFFFFFFFFu, mx = 0u, cnt = 0u;
   TSA_DEV void operator()(int16_t x, bool in) {
     const int32_t v = in ? (int32_t)x : 0;
     s += v;
     q += (uint32_t)(v * v);
     const uint32_t k = key_i16(x);
-    kmin = min(kmin, in ? k : 0xFFFFFFFFu);
-    kmax = max(kmax, in ? k : 0u);
+    mn = min(mn, in ? k : 0xFFFFFFFFu);
+    mx = max(mx, in ? k : 0u);
     if constexpr (COUNT) cnt += in ? 1u : 0u;
   }
+  TSA_DEV uint32_t kmin() const { return mn; }
+  TSA_DEV uint32_t kmax() const { return mx; }
   TSA_DEV void chunk() {}
 };
 
@@ -146,25 +206,32 @@ TSA_DEV void partial_stats(const Partial& p, int dtype, double& n, double& m, do
 // (mean - c)^2 / var costs, where c is one of the lane's own values, instead
 // of the (mean / std)^2 that unshifted sums of x and x^2 lose.  Infinities
 // seen before the first finite value add +-inf either way (c stays 0 until
-// then), so the shift is the same for every finite value of the lane.
+// then), so the shift is the same for every finite value of the lane.  Taken
+// element by element: a vec with its registers cost a block per compute unit
+// (4.3 GB: 0.73 -> 0.88 ms).
 struct ShiftMomAcc {
   double c = 0.0, s = 0.0, q = 0.0;
-  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u, cnt = 0u;
+  RawRange range;
+  uint32_t cnt = 0u;
   bool have = false;
-  TSA_DEV void operator()(float x, bool in) {
-    const bool ok = Elt<0>::valid(x, in);
-    const double v = (double)x;
-    const bool take = !have && ok && __builtin_isfinite(x);
-    c = take ? v : c;
-    have = have || take;
-    const double d = ok ? v - c : 0.0;
+  TSA_DEV void sums(float x) {
+    const double d = (double)x - c;
     s += d;
     q = __builtin_fma(d, d, q);
-    const uint32_t k = Elt<0>::key(x);
-    kmin = min(kmin, ok ? k : 0xFFFFFFFFu);
-    kmax = max(kmax, ok ? k : 0u);
-    cnt += ok ? 1u : 0u;
   }
+  TSA_DEV void operator()(float x, bool in) {
+    if (Elt<0>::valid(x, in)) {
+      if (!have && __builtin_isfinite(x)) {
+        c = (double)x;
+        have = true;
+      }
+      sums(x);
+      range.add(__float_as_uint(x));
+      ++cnt;
+    }
+  }
+  TSA_DEV uint32_t kmin() const { return range.kmin(); }
+  TSA_DEV uint32_t kmax() const { return range.kmax(); }
   TSA_DEV void chunk() {}
 };
 
@@ -195,12 +262,8 @@ TSA_DEV double wave_sum_f64(double v) {
 template <bool COUNT>
 TSA_DEV void block_store_partial(MomAcc<0, COUNT>& a, MomShared& sm, Partial* out) {
   const double s = wave_sum_f64(a.s), q = wave_sum_f64(a.q);
-  const uint32_t kmin = wave_min_u32(a.kmin), kmax = wave_max_u32(a.kmax);
-#if TSA_BALLOT_COUNT
-  const uint64_t cnt = a.cnt;  // already the wave's total
-#else
+  const uint32_t kmin = wave_min_u32(a.kmin()), kmax = wave_max_u32(a.kmax());
   const uint64_t cnt = wave_sum_u64(a.cnt);
-#endif
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   if (lane == 0) {
     sm.s[w] = s;
@@ -238,7 +301,7 @@ template <bool COUNT>
 TSA_DEV void block_store_partial(MomAcc<1, COUNT>& a, MomShared& sm, Partial* out) {
   const int64_t s = wave_sum_i64(a.s);
   const uint64_t q = wave_sum_u64(a.q);
-  const uint32_t kmin = wave_min_u32(a.kmin), kmax = wave_max_u32(a.kmax);
+  const uint32_t kmin = wave_min_u32(a.kmin()), kmax = wave_max_u32(a.kmax());
   const uint64_t cnt = wave_sum_u64(a.cnt);
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   if (lane == 0) {
@@ -293,7 +356,7 @@ TSA_DEV void block_store_centered(ShiftMomAcc& a, MomShared& sm, Partial* out) {
     const double nb = __shfl_down(n, o), mb = __shfl_down(m, o), qb = __shfl_down(m2, o);
     if (lane < o) chan_merge(n, m, m2, nb, mb, qb);
   }
-  const uint32_t kmin = wave_min_u32(a.kmin), kmax = wave_max_u32(a.kmax);
+  const uint32_t kmin = wave_min_u32(a.kmin()), kmax = wave_max_u32(a.kmax());
   if (lane == 0) {
     sm.s[w] = m;
     sm.q[w] = m2;
@@ -341,6 +404,13 @@ struct VarAcc {
     const bool ok = in && (x == x);
     const double d = (double)(ok ? x : c) - (double)c;  // masked lanes: d = 0
     q = __builtin_fma(d, d, q);
+  }
+  TSA_DEV void four(const Four& f) {  // none of them NaN
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double d = (double)f.v[e] - (double)c;
+      q = __builtin_fma(d, d, q);
+    }
   }
   TSA_DEV void chunk() {}
 };
@@ -424,34 +494,61 @@ TSA_DEV void lds_flush(const uint32_t* lds, uint32_t nbins, uint32_t rshift, uin
   }
 }
 
+// As lds_flush for a histogram whose vectors count the formula's t == nbins
+// (the value hi, rounded up) in a bin past the last instead of taking the
+// minimum for every value: that bin is the last one's.
+TSA_DEV void lds_flush_hist(const uint32_t* lds, uint32_t nbins, uint32_t rshift, uint64_t* g) {
+  const uint32_t R = 1u << rshift;
+  for (uint32_t b = threadIdx.x; b < nbins; b += blockDim.x) {
+    uint32_t c = 0;
+    for (uint32_t r = 0; r < (b + 1 == nbins ? 2 * R : R); ++r) c += lds[(b << rshift) + r];
+    if (c) atomicAdd((unsigned long long*)(g + b), (unsigned long long)c);
+  }
+}
+
 // ---- histogram (Section 4.1) ---------------------------------------------------
+// LDS: (nbins << rshift) + kTrash words (the bin past the last lies in the spare words).
+template <int DT>
 struct HistAcc {
   uint32_t* lds;
   float lo, hi, scale;
   int32_t nbm1;
   uint32_t rshift, rep;
+  uint32_t base, one;  // byte address of bin 0's replica of the lane, a 1
   uint32_t below = 0, above = 0;
+  TSA_DEV HistAcc(uint32_t* l, float lo_, float hi_, float scale_, int32_t nbins, uint32_t rshift_)
+      : lds(l), lo(lo_), hi(hi_), scale(scale_), nbm1(nbins - 1), rshift(rshift_),
+        rep(threadIdx.x & ((1u << rshift_) - 1u)), base(in_register(lds_byte_addr(l) + 4u * rep)),
+        one(in_register(1u)) {}
+  TSA_DEV void vec(const uint4& r) {
+    constexpr int N = Ty<DT>::EPV;
+    float v[N];
+    bool in = true;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      v[e] = (float)Ty<DT>::get(r, e);
+      in = in && v[e] >= lo && v[e] <= hi;  // NaN fails both tests
+    }
+    if (__ballot(!in) == 0ull) {
+#pragma unroll
+      for (int e = 0; e < N; ++e)
+        lds_add_at(((uint32_t)(int32_t)((v[e] - lo) * scale) << (rshift + 2u)) + base, one);
+    } else {
+#pragma unroll
+      for (int e = 0; e < N; ++e) (*this)(v[e], true);
+    }
+  }
   template <class T>
   TSA_DEV void operator()(T raw, bool in) {
     const float v = (float)raw;  // exact for int16
     below += (in && v < lo) ? 1u : 0u;
     above += (in && v > hi) ? 1u : 0u;
-#if TSA_BRANCHLESS
-    const float d = v - lo;
-    const float t = d * scale;  // lo == hi: scale == 0 and t == 0
-    const int32_t b = min(max((int32_t)t, 0), nbm1);
-    // out-of-range and NaN lanes count into spare words past the bins
-    const uint32_t idx = (in && v >= lo && v <= hi) ? ((uint32_t)b << rshift) + rep
-                                                    : ((uint32_t)(nbm1 + 1) << rshift) + (threadIdx.x & 63u);
-    lds_inc(lds, idx);
-#else
     if (in && v >= lo && v <= hi) {  // NaN fails both tests
       const float d = v - lo;
       const float t = d * scale;  // lo == hi: scale == 0 and t == 0
       const int32_t b = min(max((int32_t)t, 0), nbm1);
       lds_inc(lds, ((uint32_t)b << rshift) + rep);
     }
-#endif
   }
   TSA_DEV void chunk() {}
 };
@@ -465,6 +562,10 @@ struct HistOwnAcc {
   float lo, scale;
   int32_t nbm1;
   uint32_t rshift, rep;
+  uint32_t base, one;  // byte address of bin 0's replica of the lane, a 1
+  TSA_DEV HistOwnAcc(uint32_t* l, float lo_, float scale_, int32_t nbins, uint32_t rshift_)
+      : lds(l), lo(lo_), scale(scale_), nbm1(nbins - 1), rshift(rshift_), rep(threadIdx.x & ((1u << rshift_) - 1u)),
+        base(in_register(lds_byte_addr(l) + 4u * rep)), one(in_register(1u)) {}
   template <class T>
   TSA_DEV void operator()(T raw, bool in) {
     const float v = (float)raw;  // exact for int16
@@ -473,6 +574,11 @@ struct HistOwnAcc {
       const int32_t b = min((int32_t)t, nbm1);
       lds_inc(lds, ((uint32_t)b << rshift) + rep);
     }
+  }
+  TSA_DEV void four(const Four& f) {  // none of them NaN; t == nbins goes past the last bin (lds_flush_hist)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      lds_add_at(((uint32_t)(int32_t)((f.v[e] - lo) * scale) << (rshift + 2u)) + base, one);
   }
   TSA_DEV void chunk() {}
 };
@@ -500,6 +606,22 @@ struct HistWinAcc {
         atomicAdd((unsigned long long*)(counts + b), 1ull);
     }
   }
+  TSA_DEV void four(const Four& f) {  // none of them NaN
+    int32_t b[4];
+    uint32_t far = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      b[e] = min((int32_t)((f.v[e] - lo) * scale), nbm1);
+      far = max(far, (uint32_t)(b[e] - w0));
+    }
+    if (__ballot(far >= kWinBins) == 0ull) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lds_inc(lds, (uint32_t)(b[e] - w0));
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) (*this)(f.v[e], true);
+    }
+  }
   TSA_DEV void chunk() {}
 };
 
@@ -507,12 +629,32 @@ struct HistWinAcc {
 // counted apart (as HistAcc counts them), in-range values in the window
 // [w0, w0 + kWinBins) go to the LDS counters, the other in-range values to
 // the global bins.
+template <int DT>
 struct HistWinOutAcc {
   uint32_t* lds;
   float lo, hi, scale;
   int32_t nbm1, w0;
   uint64_t* counts;
   uint32_t below = 0, above = 0;
+  TSA_DEV void vec(const uint4& r) {
+    constexpr int N = Ty<DT>::EPV;
+    float v[N];
+    uint32_t rel[N];
+    bool in = true;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      v[e] = (float)Ty<DT>::get(r, e);
+      rel[e] = (uint32_t)(min((int32_t)((v[e] - lo) * scale), nbm1) - w0);
+      in = in && v[e] >= lo && v[e] <= hi && rel[e] < kWinBins;  // NaN fails
+    }
+    if (__ballot(!in) == 0ull) {
+#pragma unroll
+      for (int e = 0; e < N; ++e) lds_inc(lds, rel[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < N; ++e) (*this)(v[e], true);
+    }
+  }
   template <class T>
   TSA_DEV void operator()(T raw, bool in) {
     const float v = (float)raw;  // exact for int16
@@ -672,9 +814,13 @@ TSA_DEV uint32_t wave_scan_incl_u32(uint32_t v) {
 // cell): 32-bit DPP scans instead of 64-bit shuffles, and every wave total
 // read at once.  SH provides wsum32[16] (16-byte aligned), found, sel_digit, sel_cum32 and
 // sel_bucket32 in LDS; blockDim.x is at most 1024.
-template <class SH>
+// at(i): where counter i lies.
+struct InOrder {
+  TSA_DEV uint32_t operator()(uint32_t i) const { return i; }
+};
+template <class SH, class AT = InOrder>
 TSA_DEV bool block_select_small(const uint32_t* hist, int nb, uint32_t k, SH& sh, uint32_t* digit,
-                                uint32_t* cum_before, uint32_t* bucket) {
+                                uint32_t* cum_before, uint32_t* bucket, AT at = AT{}) {
   const int t = threadIdx.x, bs = blockDim.x;
   const int per = (nb + bs - 1) / bs;
   const int b0 = t * per;
@@ -683,11 +829,11 @@ TSA_DEV bool block_select_small(const uint32_t* hist, int nb, uint32_t k, SH& sh
     // so lanes whose runs start in the same bank read different banks (8 a run: none shared)
     for (int i = 0; i < per; ++i) {
       const int j = b0 + ((i + (t >> 3)) & (per - 1));
-      if (j < nb) local += hist[j];
+      if (j < nb) local += hist[at(j)];
     }
   } else {
     for (int i = 0; i < per; ++i)
-      if (b0 + i < nb) local += hist[b0 + i];
+      if (b0 + i < nb) local += hist[at(b0 + i)];
   }
   const int lane = t % kWave, w = t / kWave;
   const uint32_t inc = wave_scan_incl_u32(local);
@@ -706,7 +852,7 @@ TSA_DEV bool block_select_small(const uint32_t* hist, int nb, uint32_t k, SH& sh
     uint32_t cum = base;
     int d = b0;
     for (int i = 0; i < per; ++i) {
-      const uint32_t h = (b0 + i < nb) ? hist[b0 + i] : 0u;
+      const uint32_t h = (b0 + i < nb) ? hist[at(b0 + i)] : 0u;
       if (k - cum < h) {
         d = b0 + i;
         break;
@@ -715,7 +861,7 @@ TSA_DEV bool block_select_small(const uint32_t* hist, int nb, uint32_t k, SH& sh
     }
     sh.sel_digit = (uint32_t)d;
     sh.sel_cum32 = cum;
-    sh.sel_bucket32 = hist[d];
+    sh.sel_bucket32 = hist[at(d)];
     sh.found = 1;
   }
   __syncthreads();
@@ -774,20 +920,78 @@ TSA_DEV bool last_block(Arrive* a) {
 }
 
 // ---- radix digits of the key (Section 4.3 replaced by radix selection) --------
+// Counters by the top 12 bits of every valid element: of the key for int16, of
+// the bit pattern for float32 (the key's digit is digit_slot's inverse, taken
+// once per counter when they are read instead of once per value).
 template <int DT>
-struct Digit1Acc {  // top 12 key bits of every valid element
-  uint32_t* lds;
-  uint32_t rshift, rep;
+TSA_DEV uint32_t digit_slot(uint32_t d) {
+  return DT == 0 ? d ^ (d & 0x800u ? 0x800u : 0xFFFu) : d;
+}
+template <int DT>
+struct Digit1Acc {
+  uint32_t base, shift, one;  // byte address of digit 0's replica of the lane, log2 bytes per digit, a 1
+  TSA_DEV Digit1Acc(uint32_t* lds, uint32_t rshift)
+      : base(in_register(lds_byte_addr(lds) + 4u * (threadIdx.x & ((1u << rshift) - 1u)))), shift(rshift + 2u),
+        one(in_register(1u)) {}
+  TSA_DEV void add(uint32_t bits) { lds_add_at(((bits >> kShift1) << shift) + base, one); }
   template <class T>
   TSA_DEV void operator()(T raw, bool in) {
-#if TSA_BRANCHLESS
-    // invalid lanes count into spare words past the bins (one per lane)
-    const uint32_t idx = Elt<DT>::valid(raw, in) ? ((Elt<DT>::key(raw) >> kShift1) << rshift) + rep
-                                                   : ((uint32_t)kBins1 << rshift) + (threadIdx.x & 63u);
-    lds_inc(lds, idx);
-#else
-    if (Elt<DT>::valid(raw, in)) lds_inc(lds, ((Elt<DT>::key(raw) >> kShift1) << rshift) + rep);
-#endif
+    if (Elt<DT>::valid(raw, in)) {
+      if constexpr (DT == 0)
+        add(__float_as_uint(raw));
+      else
+        add(Elt<DT>::key(raw));
+    }
+  }
+  TSA_DEV void four(const Four& f) {  // none of them NaN
+#pragma unroll
+    for (int e = 0; e < 4; ++e) add(f.u[e]);
+  }
+  template <int D = DT, class = std::enable_if_t<D == 0>>
+  TSA_DEV void vec(const uint4& r) {
+    const Four f(r);
+    if (!f.wave_has_nan()) {
+      four(f);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) (*this)(f.v[e], true);
+    }
+  }
+  TSA_DEV void chunk() {}
+};
+
+// As lds_flush for Digit1Acc's counters, in key order.
+template <int DT>
+TSA_DEV void lds_flush_digits(const uint32_t* lds, uint32_t rshift, uint64_t* g) {
+  const uint32_t R = 1u << rshift;
+  for (uint32_t d = threadIdx.x; d < (uint32_t)kBins1; d += blockDim.x) {
+    uint32_t c = 0;
+    for (uint32_t r = 0; r < R; ++r) c += lds[(digit_slot<DT>(d) << rshift) + r];
+    if (c) atomicAdd((unsigned long long*)(g + d), (unsigned long long)c);
+  }
+}
+
+// Moments and first digit together (the count is the digit counters' total).
+template <int DT>
+struct Pass1Acc {
+  MomAcc<DT, false> mom;
+  Digit1Acc<DT> d1;
+  TSA_DEV Pass1Acc(uint32_t* lds, uint32_t rshift) : d1(lds, rshift) {}
+  template <class T>
+  TSA_DEV void operator()(T raw, bool in) {
+    mom(raw, in);
+    d1(raw, in);
+  }
+  template <int D = DT, class = std::enable_if_t<D == 0>>
+  TSA_DEV void vec(const uint4& r) {
+    const Four f(r);
+    if (!f.wave_has_nan()) {
+      mom.four(f);
+      d1.four(f);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) (*this)(f.v[e], true);
+    }
   }
   TSA_DEV void chunk() {}
 };
@@ -889,12 +1093,47 @@ TSA_DEV void cand_finish_block(CandSink& k) {
   __syncthreads();  // fill_w and base_b read by every wave before a later call rewrites them
 }
 
+// A first digit's bucket as an interval [lo, lo + span] of float32 bit
+// patterns, cut to non-NaN values.
+struct BitRange {
+  uint32_t lo, span;
+};
+TSA_DEV BitRange bits_of_bucket(uint32_t p1) {
+  const uint32_t k0 = max(p1 << kShift1, 0x007FFFFFu), k1 = min((p1 << kShift1) | ((1u << kShift1) - 1u), 0xFF800000u);
+  const uint32_t u0 = f32bits_of_key(k0), u1 = f32bits_of_key(k1);
+  return BitRange{min(u0, u1), max(u0, u1) - min(u0, u1)};  // a bucket has one sign
+}
+
 template <int DT>
 struct Level2Acc {  // keys inside the level-1 bucket: next 12 bits, optional copy
   uint32_t* lds;
   uint32_t p1;
   bool compact;
   CandSink sink;
+  BitRange br;  // p1's (float32)
+  // on false: no member
+  TSA_DEV Level2Acc(uint32_t* l, uint32_t prefix, bool on, bool compact_, const CandSink& k)
+      : lds(l), p1(on ? prefix >> kShift1 : 0xFFFFFFFFu), compact(on && compact_), sink(k),
+        br(on ? bits_of_bucket(prefix >> kShift1) : BitRange{0x7FFFFFFFu, 0u}) {}
+  // One subtraction and compare per value, the rest only in waves that hold a
+  // member of the bucket.
+  template <int D = DT, class = std::enable_if_t<D == 0>>
+  TSA_DEV void vec(const uint4& r) {
+    const uint32_t u[4] = {r.x, r.y, r.z, r.w};
+    bool m[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = u[e] - br.lo <= br.span;
+    if (__ballot(m[0] || m[1] || m[2] || m[3]) == 0ull) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint64_t bal = __ballot(m[e]);
+      if (bal != 0ull) {
+        const uint32_t key = key_f32(u[e]);
+        if (m[e]) lds_inc(lds, (key >> kShift2) & 0xFFFu);
+        if (compact) cand_append_slow(m[e], key, bal, sink);
+      }
+    }
+  }
   template <class T>
   TSA_DEV void operator()(T raw, bool in) {
     const uint32_t key = Elt<DT>::key(raw);
@@ -911,6 +1150,39 @@ struct Level2Acc {  // keys inside the level-1 bucket: next 12 bits, optional co
   TSA_DEV void finish() {
     if (compact) cand_finish_block(sink);
   }
+};
+
+// Histogram (counted by H), second digit and second moment together.
+template <int DT, class H>
+struct Pass2Acc {
+  H h;
+  Level2Acc<DT> l2;
+  VarAcc var;
+  bool hist_on, sel_on, var_on;
+  template <class T>
+  TSA_DEV void operator()(T raw, bool in) {
+    if (hist_on) h(raw, in);
+    l2(raw, in);
+    if constexpr (DT == 0) {
+      if (var_on) var(raw, in);
+    }
+  }
+  template <int D = DT, class = std::enable_if_t<D == 0>>
+  TSA_DEV void vec(const uint4& r) {
+    const Four f(r);
+    if (!f.wave_has_nan()) {
+      if (hist_on) h.four(f);
+      if (var_on) var.four(f);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (hist_on) h(f.v[e], true);
+        if (var_on) var(f.v[e], true);
+      }
+    }
+    if (sel_on) l2.vec(r);
+  }
+  TSA_DEV void chunk() {}
 };
 
 template <int DT>
