@@ -57,6 +57,7 @@ struct QState {
   float lo, hi, scale, shift;
   uint64_t n, k;
 };
+static_assert(sizeof(QState) == 96 && alignof(QState) == 8, "read word by word (box_view)");
 
 struct BatchHdr {
   uint64_t T1;
@@ -261,6 +262,7 @@ struct BShared {
   uint64_t t;
   uint32_t q, tile, last, flag;
   uint32_t cand_base, compact;
+  QState view;  // the box's state as the tile's phase needs it (box_view)
   Partial part;
   MomShared mom;
   alignas(16) uint32_t wsum32[16];
@@ -287,16 +289,14 @@ TSA_DEV EpScratch ep_scratch(uint32_t* lds) {
 constexpr size_t kEpLdsBytes = (size_t)kEpOffWords * 4 + (3 * 8 + 2 * 4) * (size_t)kBBlock;
 
 // Thread 0 waits until *p >= v (bounded by `limit` polls and kWaitTicks);
-// result broadcast to the block.
+// result broadcast to the block.  No acquire follows (an agent-scope acquire
+// invalidates this XCD's L2): what the block reads next it reads by box_view.
 TSA_DEV bool block_wait_ge(const uint32_t* p, uint32_t v, uint32_t* err, BShared& sh, uint32_t limit) {
   if (threadIdx.x == 0) {
     uint32_t ok = 0;
     const uint64_t t0 = wall_clock64();
     for (uint32_t it = 0; it < limit; ++it) {
-      // relaxed polls, one acquire once the value is there (an agent-scope
-      // acquire invalidates this XCD's L2)
       if (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= v) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         ok = 1;
         break;
       }
@@ -318,6 +318,17 @@ TSA_DEV bool block_wait_ge(const uint32_t* p, uint32_t v, uint32_t* err, BShared
   const bool ok = sh.flag != 0;
   __syncthreads();
   return ok;
+}
+
+// The state of a box whose epilogue has been waited for, read at the device's
+// point of coherence where the epilogue's release put it.
+TSA_DEV const QState& box_view(const QState& s, BShared& sh) {
+  const uint32_t* src = (const uint32_t*)&s;
+  uint32_t* dst = (uint32_t*)&sh.view;
+  if (threadIdx.x < sizeof(QState) / 4)
+    dst[threadIdx.x] = __hip_atomic_load(src + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  return sh.view;
 }
 
 // ---------------------------------------------------------------------------
@@ -779,7 +790,8 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
       uint32_t c = 0;  // every valid value incremented one first-digit counter
       for (int b = t; b < kBins1; b += kBBlock) c += lds[b];
       f.mom.cnt = c;
-      block_store_partial(f.mom, sh.mom, a.parts1 + a.tile_base[q] + tile);
+      block_store_partial(f.mom, sh.mom, &sh.part);  // thread 0's
+      if (t == 0) publish_partial(sh.part, a.parts1 + a.tile_base[q] + tile);
       __syncthreads();
       uint32_t* dig = a.digits + (size_t)q * kBins1;
       for (int b = t; b < kBins1; b += kBBlock) {
@@ -788,16 +800,18 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
       }
     } else if (phase == 2) {
       if (!block_wait_ge(&s.p1_ready, 1u, &a.hdr->err, sh, a.spin_limit)) return;
-      if (!s.skip2) {
+      const QState& v = box_view(s, sh);
+      if (!v.skip2) {
         const uint32_t hsize = ((uint32_t)a.nbins << a.rshift) + kTrash;
         uint32_t* l2 = lds + hsize;
         lds_zero(lds, hsize + kBins2);
         __syncthreads();
-        const bool hist_on = s.hist_ok != 0, var_on = DT == 0 && s.var_on != 0;
+        const bool hist_on = v.hist_ok != 0, var_on = DT == 0 && v.var_on != 0;
         Pass2Acc<DT, HistOwnAcc> f{
-            HistOwnAcc(lds, s.lo, s.scale, a.nbins, a.rshift),
-            Level2Acc<DT>(l2, s.prefix, true, s.compact != 0, cand_sink(cs, a.pool + s.cand_base, &s.cand_fill, s.cand_n)),
-            VarAcc{s.shift}, hist_on, true, var_on};
+            HistOwnAcc(lds, v.lo, v.scale, a.nbins, a.rshift),
+            Level2Acc<DT>(l2, v.prefix, true, v.compact != 0,
+                          cand_sink(cs, a.pool + v.cand_base, &s.cand_fill, v.cand_n, true)),
+            VarAcc{v.shift}, hist_on, true, var_on};
         walk_tile<DT, VEC, NT>(a, g, tile, f);
         f.l2.finish();
         __syncthreads();
@@ -816,27 +830,26 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
           if (t == 0) {
             double bq = sh.mom.q[0];
             for (int i = 1; i < kBBlock / kWave; ++i) bq += sh.mom.q[i];
-            a.parts2[a.tile_base[q] + tile] = bq;
+            __hip_atomic_store(a.parts2 + a.tile_base[q] + tile, bq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
         }
       }
     } else {
       // only a box left without a candidate copy can need the last digit
       if (!block_wait_ge(&s.p1_ready, 1u, &a.hdr->err, sh, a.spin_limit)) return;
-      if (t == 0) sh.flag = (DT == 0 && s.skip2 == 0 && s.compact == 0) ? 1u : 0u;
-      __syncthreads();
-      const bool may3 = sh.flag != 0;
+      const QState& v = box_view(s, sh);
+      const bool may3 = DT == 0 && v.skip2 == 0 && v.compact == 0;
       __syncthreads();
       if (!may3) continue;
       if (!block_wait_ge(&s.p2_ready, 1u, &a.hdr->err, sh, a.spin_limit)) return;
-      if (t == 0) sh.flag = s.need3;
-      __syncthreads();
-      const bool need3 = sh.flag != 0;
+      box_view(s, sh);  // v again, as the second epilogue left it
+      const bool need3 = v.need3 != 0;
+      const uint32_t p3 = v.prefix >> kShift2;
       __syncthreads();
       if (!need3) continue;
       lds_zero(lds, kBins3);
       __syncthreads();
-      Level3Acc<DT> f{lds, s.prefix >> kShift2};
+      Level3Acc<DT> f{lds, p3};
       walk_tile<DT, VEC, NT>(a, g, tile, f);
       __syncthreads();
       uint32_t* dig = a.digits + (size_t)q * kBins1;
@@ -848,13 +861,13 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
     // count the tile; the block finishing the last one runs the epilogue
     block_writes_done();
     if (t == 0) {
-      // the release publishes this tile's partial and counters (the block's
-      // writes precede it through the barrier above); only the block that
-      // counts the last tile acquires, since only it reads the others' work.
-      // Each agent-scope release writes back this XCD's L2 and each acquire
-      // invalidates it, so a tile pays one of the first and none of the second.
+      // everything the tile leaves for others it wrote by agent-scope atomics
+      // (partials, counters, candidates), and the barrier above waited for
+      // them: the count needs no release, which would write back this XCD's
+      // L2 for every tile (256 boxes of edges up to 90: 292 -> 140 us).
+      // Only the block that counts the last tile acquires.
       uint32_t* cnt = phase == 1 ? &s.done1 : phase == 2 ? &s.done2 : &s.done3;
-      const uint32_t prev = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t prev = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       sh.last = prev + 1 == g.ntiles ? 1u : 0u;
       if (sh.last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }

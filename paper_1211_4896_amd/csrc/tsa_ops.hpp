@@ -1023,16 +1023,25 @@ struct CandSink {
   uint32_t cap;       // global capacity
   uint32_t stage;     // keys per wave the stage holds
   uint32_t fill;      // keys this wave has staged (equal in every lane)
+  bool publish;       // another block of the same launch reads the list (agent-scope stores)
 };
+TSA_DEV void cand_put(const CandSink& k, uint32_t at, uint32_t key) {
+  if (at >= k.cap) return;
+  if (k.publish)
+    __hip_atomic_store(k.list + at, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    k.list[at] = key;
+}
 
 template <int NW, uint32_t S>
-TSA_DEV CandSink cand_sink(CandSharedN<NW, S>& cs, uint32_t* list, uint32_t* counter, uint32_t cap) {
-  return CandSink{&cs.buf[0][0], list, counter, cap, S, 0u};
+TSA_DEV CandSink cand_sink(CandSharedN<NW, S>& cs, uint32_t* list, uint32_t* counter, uint32_t cap,
+                           bool publish = false) {
+  return CandSink{&cs.buf[0][0], list, counter, cap, S, 0u, publish};
 }
 
 // Staging carved from dynamic LDS: `stage` words per wave of the block.
 TSA_DEV CandSink cand_sink_lds(uint32_t* base, uint32_t stage, uint32_t* list, uint32_t* counter, uint32_t cap) {
-  return CandSink{base, list, counter, cap, stage, 0u};
+  return CandSink{base, list, counter, cap, stage, 0u, false};
 }
 
 // The wave copies its `fill` staged keys out (one global atomic).  Whole wave.
@@ -1042,8 +1051,7 @@ TSA_DEV void cand_copy_out(const CandSink& k, uint32_t fill) {
   uint32_t g = 0;
   if (lane == 0) g = atomicAdd(k.counter, fill);
   g = __builtin_amdgcn_readfirstlane(g);  // lane 0's result, without an LDS permute
-  for (uint32_t i = lane; i < fill; i += kWave)
-    if (g + i < k.cap) k.list[g + i] = k.buf[w * k.stage + i];
+  for (uint32_t i = lane; i < fill; i += kWave) cand_put(k, g + i, k.buf[w * k.stage + i]);
   __builtin_amdgcn_wave_barrier();  // and the reads finish before the stage is refilled
 }
 
@@ -1087,8 +1095,7 @@ TSA_DEV void cand_finish_block(CandSink& k) {
   __syncthreads();
   uint32_t g = base_b;
   for (int i = 0; i < w; ++i) g += fill_w[i];
-  for (uint32_t i = lane; i < k.fill; i += kWave)
-    if (g + i < k.cap) k.list[g + i] = k.buf[w * k.stage + i];
+  for (uint32_t i = lane; i < k.fill; i += kWave) cand_put(k, g + i, k.buf[w * k.stage + i]);
   k.fill = 0;
   __syncthreads();  // fill_w and base_b read by every wave before a later call rewrites them
 }
