@@ -75,55 +75,67 @@ __global__ __launch_bounds__(1024) void k_hist(Geom g, float lo, float hi, float
 // ---------------------------------------------------------------------------
 // histograms of more bins than one LDS copy holds (the standalone call)
 // ---------------------------------------------------------------------------
-// Where the window of kWinBins 32-bit LDS counters goes: one block bins a
-// sample of 64 voxels per lane spread evenly over the region (the stated
-// formula), counts them per group of nbins/256 bins, and writes the first bin
-// of the run of groups that holds the most samples.  Only the placement
-// depends on the sample; k_hist_win counts every voxel exactly wherever the
-// window is.
-constexpr int kPlaceThreads = 1024, kPlacePerLane = 64;
+// Where the window of kWinBins 32-bit LDS counters goes: 65536 voxels spread
+// evenly over the region are binned (the stated formula) and counted per group
+// of nbins/256 bins; the block that ends last writes the first bin of the run
+// of groups that holds the most.  Only the placement depends on the sample;
+// k_hist_win counts every voxel exactly wherever the window is.  Bound by the
+// latency of the scattered loads, so one per lane over 64 blocks (one block
+// with 64 per lane took 85 to 150 us).
+constexpr int kPlaceThreads = 1024, kPlaceBlocks = 64, kPlaceGroups = 256;
 
 template <int DT>
 __global__ __launch_bounds__(kPlaceThreads) void k_hist_place(const void* base, int64_t nx, int64_t ny, tsa_region b,
                                                               float lo, float hi, float scale, int32_t nbins,
+                                                              uint32_t* __restrict__ groups, Arrive* arrive,
                                                               int32_t* __restrict__ w0_out) {
   using T = typename Ty<DT>::T;
-  __shared__ uint32_t coarse[256];
-  uint32_t gshift = 0;  // bins per group: 2^gshift, at most 256 groups
-  while (((uint32_t)(nbins - 1) >> gshift) >= 256u) ++gshift;
-  for (int i = threadIdx.x; i < 256; i += blockDim.x) coarse[i] = 0u;
+  __shared__ uint32_t coarse[kPlaceGroups], below[kPlaceGroups + 1];
+  __shared__ uint64_t best;
+  const int t = threadIdx.x;
+  uint32_t gshift = 0;  // bins per group: 2^gshift, at most kPlaceGroups groups
+  while (((uint32_t)(nbins - 1) >> gshift) >= (uint32_t)kPlaceGroups) ++gshift;
+  if (t < kPlaceGroups) coarse[t] = 0u;
   __syncthreads();
   const int64_t lx = b.x1 - b.x0, ly = b.y1 - b.y0, lz = b.z1 - b.z0;
   const uint64_t vol = (uint64_t)lx * (uint64_t)ly * (uint64_t)lz;
-  const uint64_t ns = (uint64_t)kPlaceThreads * kPlacePerLane;
-  for (int k = 0; k < kPlacePerLane; ++k) {
-    const uint64_t s = (uint64_t)k * kPlaceThreads + threadIdx.x;
-    const uint64_t i = (uint64_t)(((unsigned __int128)s * vol) / ns);  // < vol
-    const int64_t x = (int64_t)(i % (uint64_t)lx), r = (int64_t)(i / (uint64_t)lx);
-    const int64_t y = r % ly, z = r / ly;
-    const float v = (float)((const T*)base)[(b.z0 + z) * nx * ny + (b.y0 + y) * nx + (b.x0 + x)];
-    if (v >= lo && v <= hi) {
-      const int32_t bin = min(max((int32_t)((v - lo) * scale), 0), nbins - 1);
-      atomicAdd(&coarse[(uint32_t)bin >> gshift], 1u);
-    }
+  const uint64_t ns = (uint64_t)kPlaceThreads * kPlaceBlocks, s = (uint64_t)blockIdx.x * kPlaceThreads + t;
+  const uint64_t i = (uint64_t)(((unsigned __int128)s * vol) / ns);  // < vol
+  const int64_t x = (int64_t)(i % (uint64_t)lx), r = (int64_t)(i / (uint64_t)lx);
+  const int64_t y = r % ly, z = r / ly;
+  const float v = (float)((const T*)base)[(b.z0 + z) * nx * ny + (b.y0 + y) * nx + (b.x0 + x)];
+  if (v >= lo && v <= hi) {
+    const int32_t bin = min(max((int32_t)((v - lo) * scale), 0), nbins - 1);
+    atomicAdd(&coarse[(uint32_t)bin >> gshift], 1u);
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int32_t ngroups = (int32_t)(((uint32_t)(nbins - 1) >> gshift) + 1);
-    const int32_t wg = min((int32_t)(kWinBins >> gshift), ngroups);  // groups the window spans
-    uint32_t run = 0;
-    for (int32_t g = 0; g < wg; ++g) run += coarse[g];
-    uint32_t best = run;
-    int32_t best_g = 0;
-    for (int32_t g = 1; g + wg <= ngroups; ++g) {
-      run += coarse[g + wg - 1];
-      run -= coarse[g - 1];
-      if (run > best) {
-        best = run;
-        best_g = g;
-      }
+  if (t < kPlaceGroups && coarse[t]) atomicAdd(groups + t, coarse[t]);
+  if (!last_block(arrive)) return;
+  if (t == 0) {
+    best = 0;
+    below[0] = 0;
+  }
+  if (t < kPlaceGroups) coarse[t] = groups[t];
+  __syncthreads();
+  if (t < kWave) {  // below[g]: samples in groups before g
+    uint32_t c[kPlaceGroups / kWave], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPlaceGroups / kWave; ++k) {
+      sum += coarse[t * (kPlaceGroups / kWave) + k];
+      c[k] = sum;
     }
-    int32_t w0 = best_g << gshift;
+    const uint32_t before = wave_scan_incl_u32(sum) - sum;
+#pragma unroll
+    for (int k = 0; k < kPlaceGroups / kWave; ++k) below[t * (kPlaceGroups / kWave) + k + 1] = before + c[k];
+  }
+  __syncthreads();
+  const int32_t ngroups = (int32_t)(((uint32_t)(nbins - 1) >> gshift) + 1);
+  const int32_t wg = min((int32_t)(kWinBins >> gshift), ngroups);  // groups the window spans
+  if (t + wg <= ngroups)  // the fullest run, the first of equals
+    atomicMax((unsigned long long*)&best, ((unsigned long long)(below[t + wg] - below[t]) << 32) | (uint32_t)(kPlaceGroups - t));
+  __syncthreads();
+  if (t == 0) {
+    int32_t w0 = (kPlaceGroups - (int32_t)(uint32_t)best) << gshift;
     if (w0 > nbins - (int32_t)kWinBins) w0 = max(nbins - (int32_t)kWinBins, 0);
     *w0_out = w0;
   }
@@ -1298,11 +1310,14 @@ int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, floa
   int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcHist);
   if (st) return st;
   uint64_t* outl = d_outliers ? d_outliers : (uint64_t*)(P.ws + P.L.outl);
-  fill_set({FillRange{(uint32_t*)d_counts, (uint64_t)nbins * 2, 0u, 0u}, FillRange{(uint32_t*)outl, 4u, 0u, 0u}},
-           P.s);
   const size_t budget = P.dev.lds_per_block < 65536 ? P.dev.lds_per_block : 65536;
   const uint32_t rs = rep_shift_for(nbins, budget);
   const size_t lds = (((size_t)nbins << rs) + kTrash) * 4;
+  uint32_t* groups = (uint32_t*)(P.ws + P.L.hist1);  // of the window's placement
+  fill_set({FillRange{(uint32_t*)d_counts, (uint64_t)nbins * 2, 0u, 0u}, FillRange{(uint32_t*)outl, 4u, 0u, 0u},
+            FillRange{groups, lds <= budget ? 0u : (uint64_t)kPlaceGroups, 0u, 0u},
+            FillRange{(uint32_t*)arrive_of(P, 0), lds <= budget ? 0u : sizeof(Arrive) / 4, 0u, 0u}},
+           P.s);
   if (lds <= budget) {
     TSA_TRACED("hist", P.s,
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
@@ -1317,12 +1332,12 @@ int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, floa
     int32_t* w0p = (int32_t*)(P.ws + P.L.state + offsetof(SelState, win0));
     if (cube->dtype == TSA_F32)
       TSA_TRACED("hist_place", P.s,
-                 hipLaunchKernelGGL(k_hist_place<0>, dim3(1), dim3(kPlaceThreads), 0, P.s, cube->data, cube->nx,
-                                    cube->ny, P.box, lo, hi, scale, nbins, w0p));
+                 hipLaunchKernelGGL(k_hist_place<0>, dim3(kPlaceBlocks), dim3(kPlaceThreads), 0, P.s, cube->data,
+                                    cube->nx, cube->ny, P.box, lo, hi, scale, nbins, groups, arrive_of(P, 0), w0p));
     else
       TSA_TRACED("hist_place", P.s,
-                 hipLaunchKernelGGL(k_hist_place<1>, dim3(1), dim3(kPlaceThreads), 0, P.s, cube->data, cube->nx,
-                                    cube->ny, P.box, lo, hi, scale, nbins, w0p));
+                 hipLaunchKernelGGL(k_hist_place<1>, dim3(kPlaceBlocks), dim3(kPlaceThreads), 0, P.s, cube->data,
+                                    cube->nx, cube->ny, P.box, lo, hi, scale, nbins, groups, arrive_of(P, 0), w0p));
     int grid = P.dev.cus;
     if (grid > P.grid) grid = P.grid;
     int stw = TSA_OK;
