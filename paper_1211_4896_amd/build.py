@@ -16,7 +16,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtsa.so")
 OBJDIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["tsa_kernels.hip", "tsa_hist_wide.hip", "tsa_count16.hip", "tsa_batch.hip", "tsa_serve.hip", "tsa_tune.hip",
+SOURCES = ["tsa_kernels.hip", "tsa_hist_wide.hip", "tsa_count16.hip", "tsa_bracket.hip",
+           "tsa_batch.hip", "tsa_serve.hip", "tsa_tune.hip",
            "tsa_minimap.hip", "tsa_spectrum.hip", "tsa_trace.hip", "tsa_api.hip"]
 
 HIPCC_FLAGS = [

@@ -92,6 +92,19 @@ int count16_mode(int64_t volume, int grid, size_t table_bytes, const Count16Ask&
 int run_count16(const Geom& g, int vec, int grid, int mode, void* scratch, void* small, void* tables,
                 const Count16Ask& ask, hipStream_t s);
 
+// Ranks of float32 regions from a bracket (tsa_bracket.hip).
+struct BracketAsk {
+  tsa_result* out;
+  double* qout;  // null: none
+  uint64_t volume;
+  int32_t write_counts;
+};
+size_t bracket_bytes();
+uint32_t bracket_samples(int64_t volume, uint32_t cand_cap);
+int run_bracket(const tsa_cube* cube, const tsa_region& box, const Geom& g, int vec, bool nt, int grid, int block,
+                void* mem, uint32_t ns, uint32_t* cand, uint32_t cand_cap, void* parts, SelState* st,
+                const SelState* med, const BracketAsk& ask, hipStream_t s);
+
 int run_moments(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out, void* d_ws, size_t ws_bytes,
                 tsa_stream_t stream);
 int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, float hi, int32_t nbins,

@@ -312,6 +312,7 @@ template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_level1(Geom g, uint32_t rshift, SelState* __restrict__ st,
                                                  uint64_t* __restrict__ hist1, Tail tl) {
   extern __shared__ uint32_t lds[];
+  if (st->done) return;
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
   Digit1Acc<DT> d(lds, rshift);
@@ -507,7 +508,7 @@ template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_mlevel1(Geom g, uint32_t rshift, const SelState* __restrict__ med,
                                                   SelState* __restrict__ st, uint64_t* __restrict__ hist1, Tail tl) {
   extern __shared__ uint32_t lds[];
-  if (!med->done || med->n == 0) return;  // no value: st is left unfinished
+  if (!med->done || med->n == 0 || st->done) return;  // no value: st is left unfinished
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
   float mf;
@@ -1232,11 +1233,13 @@ static SelState first_state(const Prep& P, double q, int32_t levels) {
 // Zero the arrival counters and the level histograms, set the selection state, and clear the caller's
 // output counters (d_counts: nbins u64, outl: 2 u64; null for none), all in
 // one launch.
+// (more: the words of a bracket's memory, from the histogram copies' place on.)
 static void reset_select(const Prep& P, const SelState& init, uint64_t* d_counts = nullptr, int32_t nbins = 0,
-                         uint64_t* outl = nullptr) {
+                         uint64_t* outl = nullptr, size_t more = 0) {
   fill_set({FillRange{(uint32_t*)(P.ws + P.L.arrive), (uint64_t)(P.L.state - P.L.arrive) / 4, 0u, 0u},
             FillRange{(uint32_t*)d_counts, d_counts ? (uint64_t)nbins * 2 : 0u, 0u, 0u},
-            FillRange{(uint32_t*)outl, outl ? 4u : 0u, 0u, 0u}},
+            FillRange{(uint32_t*)outl, outl ? 4u : 0u, 0u, 0u},
+            FillRange{(uint32_t*)(P.ws + P.L.hcopy), more / 4, 0u, 0u}},
            P.s, (SelState*)(P.ws + P.L.state), init);
 }
 
@@ -1349,8 +1352,20 @@ int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, floa
   return run_histogram_wide(cube, P.g, P.vec, P.grid, P.block, lo, hi, scale, nbins, d_counts, outl, P.s);
 }
 
+// Voxels to sample when the region's ranks are bracketed first (0: they are not).
+static uint32_t bracket_of(const tsa_cube* cube, const Prep& P) {
+  return cube->dtype == TSA_F32 ? bracket_samples(P.volume, P.L.cand_cap) : 0u;
+}
+// The bracket of the rank that st holds (of the deviations from *med, where given), its memory at `mem`.
+static int launch_bracket_of(const tsa_cube* cube, const Prep& P, uint32_t ns, char* mem, SelState* st,
+                             const SelState* med, const Tail& tl) {
+  return run_bracket(cube, P.box, P.g, P.vec, tuning().nt, P.grid, P.block, mem, ns, (uint32_t*)(P.ws + P.L.cand),
+                     P.L.cand_cap, P.ws + P.L.partials, st, med,
+                     BracketAsk{tl.out, tl.qout, tl.volume, tl.write_counts}, P.s);
+}
+
 // The three passes of a selection over the region, each choosing its digit in
-// its last block.
+// its last block; they end at once when a bracket has found the value.
 static int launch_selection(const tsa_cube* cube, const Prep& P, const Tail& tl) {
   SelState* stp = (SelState*)(P.ws + P.L.state);
   uint64_t* h1 = (uint64_t*)(P.ws + P.L.hist1);
@@ -1384,8 +1399,12 @@ int run_median(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out
   ask.rank = 1;
   ask.write_counts = 1;
   if (try_count16(cube, P, ask, &st)) return st;
-  reset_select(P, first_state(P));
-  return launch_selection(cube, P, Tail{d_out, nullptr, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 1});
+  const uint32_t ns = bracket_of(cube, P);
+  const Tail tl{d_out, nullptr, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 1};
+  reset_select(P, first_state(P), nullptr, 0, nullptr, ns ? bracket_bytes() : 0);
+  if (ns && (st = launch_bracket_of(cube, P, ns, P.ws + P.L.hcopy, (SelState*)(P.ws + P.L.state), nullptr, tl)))
+    return st;
+  return launch_selection(cube, P, tl);
 }
 
 // ---------------------------------------------------------------------------
@@ -1728,9 +1747,13 @@ int run_quantile(const tsa_cube* cube, const tsa_region* region, double q, int32
   ask.q = q;
   ask.digits = digits;
   if (try_count16(cube, P, ask, &st)) return st;
-  reset_select(P, first_state(P, q, digits));
+  const uint32_t ns = digits == 3 ? bracket_of(cube, P) : 0u;
+  reset_select(P, first_state(P, q, digits), nullptr, 0, nullptr, ns ? bracket_bytes() : 0);
   tsa_result* scratch = (tsa_result*)(P.ws + P.L.result);
-  return launch_selection(cube, P, Tail{scratch, d_out, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 0});
+  const Tail tl{scratch, d_out, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 0};
+  if (ns && (st = launch_bracket_of(cube, P, ns, P.ws + P.L.hcopy, (SelState*)(P.ws + P.L.state), nullptr, tl)))
+    return st;
+  return launch_selection(cube, P, tl);
 }
 
 int run_mad(const tsa_cube* cube, const tsa_region* region, double* d_out, void* d_ws, size_t ws_bytes,
@@ -1752,15 +1775,22 @@ int run_mad(const tsa_cube* cube, const tsa_region* region, double* d_out, void*
   uint64_t* m1 = (uint64_t*)(P.ws + P.L.hcopy);
   uint64_t* m2 = m1 + kBins1;
   uint64_t* m3 = m2 + kBins2;
+  // and behind them the memory of the two brackets
+  constexpr size_t kDigits = 8 * (size_t)(kBins1 + kBins2 + kBins3);
+  const uint32_t ns = bracket_of(cube, P);
+  char* mem = (char*)m1 + kDigits;
   const SelState init = first_state(P);
   fill_set({FillRange{(uint32_t*)(P.ws + P.L.arrive), (uint64_t)(P.L.state - P.L.arrive) / 4, 0u, 0u},
-            FillRange{(uint32_t*)m1, 2ull * (kBins1 + kBins2 + kBins3), 0u, 0u}},
+            FillRange{(uint32_t*)m1, (kDigits + (ns ? 2 * bracket_bytes() : 0)) / 4, 0u, 0u}},
            P.s, med, init, sb, init);
   // 1. the lower median m
-  st = launch_selection(cube, P, Tail{scratch, nullptr, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 0});
+  const Tail tlm{scratch, nullptr, (uint64_t)P.volume, arrive_of(P, 0), cube->dtype, 0};
+  if (ns && (st = launch_bracket_of(cube, P, ns, mem, med, nullptr, tlm))) return st;
+  st = launch_selection(cube, P, tlm);
   if (st) return st;
   // 2. the lower median of |x - m| (float keys whatever the cube's type)
   const Tail tl{scratch, nullptr, (uint64_t)P.volume, arrive_of(P, 3), 0, 0};
+  if (ns && (st = launch_bracket_of(cube, P, ns, mem + bracket_bytes(), sb, med, tl))) return st;
   const uint32_t rs = rep_shift_for(kBins1, 32768);
   TSA_TRACED("mad_level1", P.s,
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
