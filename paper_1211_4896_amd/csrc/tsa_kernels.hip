@@ -45,11 +45,11 @@ __global__ __launch_bounds__(1024) void k_moments(Geom g, Partial* __restrict__ 
   __shared__ MomShared sm;
   if constexpr (DT == 0) {
     ShiftMomAcc acc;
-    walk<DT, VEC, kUnroll, NT>(g, acc);
+    walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, acc);
     block_store_centered(acc, sm, parts + blockIdx.x);
   } else {
     MomAcc<DT> acc;
-    walk<DT, VEC, kUnroll, NT>(g, acc);
+    walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, acc);
     block_store_partial(acc, sm, parts + blockIdx.x);
   }
 }
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(1024) void k_hist(Geom g, float lo, float hi, float
   lds_zero(lds, ((uint32_t)nbins << rshift) + kTrash);
   __syncthreads();
   HistAcc<DT> h(lds, lo, hi, scale, nbins, rshift);
-  walk<DT, VEC, kUnroll, NT>(g, h);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, h);
   __syncthreads();
   lds_flush_hist(lds, (uint32_t)nbins, rshift, counts);
   block_add_outliers(h.below, h.above, outl, osm);
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(1024) void k_hist_win(Geom g, float lo, float hi, f
   lds_zero(lds, kWinBins);
   __syncthreads();
   HistWinOutAcc<DT> h{lds, lo, hi, scale, nbins - 1, w0, counts};
-  walk<DT, VEC, kUnroll, NT>(g, h);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, h);
   __syncthreads();
   const uint32_t nw = (uint32_t)min((int32_t)kWinBins, nbins - w0);
   for (uint32_t i = threadIdx.x; i < nw; i += blockDim.x) {
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(1024) void k_level1(Geom g, uint32_t rshift, SelSta
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
   Digit1Acc<DT> d(lds, rshift);
-  walk<DT, VEC, kUnroll, NT>(g, d);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, d);
   __syncthreads();
   lds_flush_digits<DT>(lds, rshift, hist1);
   select_tail(1, hist1, st, tl);
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(1024) void k_level2(Geom g, SelState* __restrict__ 
   lds_zero(lds, kBins2);
   __syncthreads();
   Level2Acc<DT> a(lds, st->prefix, true, st->compact != 0, cand_sink(cs, cand, &st->ncand, st->cand_cap));
-  walk<DT, VEC, kUnroll, NT>(g, a);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, a);
   a.finish();
   __syncthreads();
   lds_flush(lds, kBins2, 0, hist2);
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(1024) void k_level3(Geom g, SelState* __restrict__ 
     }
   } else {
     Level3Acc<DT> a{lds, p2};
-    walk<DT, VEC, kUnroll, NT>(g, a);
+    walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, a);
   }
   __syncthreads();
   lds_flush(lds, kBins3, 0, hist3);
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(1024) void k_mlevel1(Geom g, uint32_t rshift, const
   int32_t mi;
   median_of_state<DT>(med, mf, mi);
   AbsDev<DT, Digit1Acc<0>> a{Digit1Acc<0>(lds, rshift), mf, mi};
-  walk<DT, VEC, kUnroll, NT>(g, a);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, a);
   __syncthreads();
   lds_flush_digits<0>(lds, rshift, hist1);
   select_tail(1, hist1, st, tl);
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(1024) void k_mlevel2(Geom g, const SelState* __rest
   median_of_state<DT>(med, mf, mi);
   AbsDev<DT, Level2Acc<0>> a{
       Level2Acc<0>(lds, st->prefix, true, st->compact != 0, cand_sink(cs, cand, &st->ncand, st->cand_cap)), mf, mi};
-  walk<DT, VEC, kUnroll, NT>(g, a);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, a);
   a.inner.finish();
   __syncthreads();
   lds_flush(lds, kBins2, 0, hist2);
@@ -577,7 +577,7 @@ __global__ __launch_bounds__(1024) void k_mlevel3(Geom g, const SelState* __rest
     int32_t mi;
     median_of_state<DT>(med, mf, mi);
     AbsDev<DT, Level3Acc<0>> a{Level3Acc<0>{lds, p2}, mf, mi};
-    walk<DT, VEC, kUnroll, NT>(g, a);
+    walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, a);
   }
   __syncthreads();
   lds_flush(lds, kBins3, 0, hist3);
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(1024) void k_pass_a(Geom g, uint32_t rshift, Partia
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
   Pass1Acc<DT> a(lds, rshift);
-  walk<DT, VEC, kUnroll, NT, DT == 0>(g, a);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT, DT == 0>(g, a);
   // every valid value incremented one first-digit counter: the block's count
   // is their total (each lane adds a strided share; the partial sums them)
   __syncthreads();
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t
   Pass2Acc<DT, HistOwnAcc> b{HistOwnAcc(lds, st->lo, st->scale, nbins, rshift),
                              Level2Acc<DT>(l2, st->prefix, sel_on, st->compact != 0, sink), VarAcc{st->shift},
                              hist_on, sel_on, var_on};
-  walk<DT, VEC, kUnroll, NT>(g, b);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, b);
   b.l2.finish();
   __syncthreads();
   // into one of kHistCopies copies (counts holds them nbins apart), summed by k_level3
@@ -789,7 +789,7 @@ __global__ __launch_bounds__(1024) void k_pass_bwin(Geom g, int32_t nbins, SelSt
   Pass2Acc<DT, HistWinAcc> b{HistWinAcc{lds, st->lo, st->scale, nbins - 1, w0, counts},
                              Level2Acc<DT>(l2, st->prefix, sel_on, st->compact != 0, sink), VarAcc{st->shift},
                              hist_on, sel_on, var_on};
-  walk<DT, VEC, kUnroll, NT>(g, b);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, b);
   b.l2.finish();
   __syncthreads();
   if (hist_on) {
@@ -850,7 +850,7 @@ __global__ __launch_bounds__(1024) void k_pass_b16(Geom g, int32_t nbins, uint32
                 Level2Acc<DT>(l2, st->prefix, sel_on, st->compact != 0,
                               cand_sink(cs, cand, &st->ncand, st->cand_cap)),
                 VarAcc{st->shift}, hist_on, var_on};
-  walk<DT, VEC, kUnroll, NT>(g, b);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, b);
   b.l2.finish();
   if (hist_on) b.h.flush();
   __syncthreads();
