@@ -195,12 +195,7 @@ TSA_DEV void select_level(int level, const uint64_t* __restrict__ hist, SelState
   for (int i = 0; i < 16; ++i) local += h[i];
   // block exclusive scan of `local`
   const int lane = t % kWave, w = t / kWave;
-  uint64_t inc = local;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint64_t y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
-  }
+  const uint64_t inc = wave_scan_incl_u64(local);
   if (lane == kWave - 1) sm.wsum[w] = inc;
   if (t == 0) sm.found = 0;
   __syncthreads();

@@ -430,7 +430,12 @@ __global__ __launch_bounds__(kMMBlock) __attribute__((amdgpu_waves_per_eu(EPT <=
   for (int j = 0; j < EPT; ++j) asm volatile("" : "+v"(x[j]));
   {
     uint32_t c = 0;
-    for (uint32_t i = t; i < kBins1; i += kMMBlock) c += dig[i];
+#pragma unroll
+    for (uint32_t i = 0; i < kBins1; i += kMMBlock) {  // every read in flight at once
+      const uint32_t b = i + (uint32_t)t;
+      const uint32_t d = dig[min(b, (uint32_t)kBins1)];  // (past them: a spare word, never written)
+      c += b < (uint32_t)kBins1 ? d : 0u;
+    }
     mom.cnt = c;
   }
   block_store_partial(mom, sh.mom, &sh.part);  // ends with thread 0 writing sh.part

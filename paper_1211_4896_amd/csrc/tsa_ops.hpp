@@ -253,12 +253,6 @@ struct alignas(16) MomShared {
   uint64_t cnt[16];
 };
 
-TSA_DEV double wave_sum_f64(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);  // a + b == b + a: every lane ends equal
-  return v;
-}
-
 template <bool COUNT>
 TSA_DEV void block_store_partial(MomAcc<0, COUNT>& a, MomShared& sm, Partial* out) {
   const double s = wave_sum_f64(a.s), q = wave_sum_f64(a.q);
@@ -273,27 +267,18 @@ TSA_DEV void block_store_partial(MomAcc<0, COUNT>& a, MomShared& sm, Partial* ou
     sm.cnt[w] = cnt;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int nw = blockDim.x / kWave;
-    double bs = sm.s[0], bq = sm.q[0];
-    uint32_t mn = sm.kmin[0], mx = sm.kmax[0];
-    uint64_t n = sm.cnt[0];
-    for (int i = 1; i < nw; ++i) {
-      bs += sm.s[i];
-      bq += sm.q[i];
-      mn = min(mn, sm.kmin[i]);
-      mx = max(mx, sm.kmax[i]);
-      n += sm.cnt[i];
-    }
+  if (w == 0) {  // the waves' sums by the first wave (a lane each, all read at once)
+    const bool on = lane < (int)(blockDim.x / kWave);
+    const int i = on ? lane : 0;
     Partial p;
-    p.n = n;
-    p.kmin = mn;
-    p.kmax = mx;
-    p.s = bs;
-    p.q = bq;
+    p.n = wave_sum_u64(on ? sm.cnt[i] : 0ull);
+    p.kmin = wave_min_u32(sm.kmin[i]);
+    p.kmax = wave_max_u32(sm.kmax[i]);
+    p.s = wave_sum_f64(on ? sm.s[i] : 0.0);
+    p.q = wave_sum_f64(on ? sm.q[i] : 0.0);
     p.si = 0;
     p.qi = 0;
-    *out = p;
+    if (lane == 0) *out = p;
   }
 }
 
@@ -312,23 +297,17 @@ TSA_DEV void block_store_partial(MomAcc<1, COUNT>& a, MomShared& sm, Partial* ou
     sm.cnt[w] = cnt;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int nw = blockDim.x / kWave;
+  if (w == 0) {
+    const bool on = lane < (int)(blockDim.x / kWave);
+    const int i = on ? lane : 0;
     Partial p;
-    p.n = 0;
-    p.si = 0;
-    p.qi = 0;
-    p.kmin = 0xFFFFFFFFu;
-    p.kmax = 0u;
-    for (int i = 0; i < nw; ++i) {
-      p.si += sm.si[i];
-      p.qi += sm.qi[i];
-      p.kmin = min(p.kmin, sm.kmin[i]);
-      p.kmax = max(p.kmax, sm.kmax[i]);
-      p.n += sm.cnt[i];
-    }
+    p.n = wave_sum_u64(on ? sm.cnt[i] : 0ull);
+    p.kmin = wave_min_u32(sm.kmin[i]);
+    p.kmax = wave_max_u32(sm.kmax[i]);
+    p.si = wave_sum_i64(on ? sm.si[i] : 0ll);
+    p.qi = wave_sum_u64(on ? sm.qi[i] : 0ull);
     p.s = p.q = 0.0;
-    *out = p;
+    if (lane == 0) *out = p;
   }
 }
 
@@ -420,18 +399,16 @@ TSA_DEV void block_store_var(VarAcc& a, MomShared& sm, Partial* out) {
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   if (lane == 0) sm.q[w] = q;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int nw = blockDim.x / kWave;
-    double bq = sm.q[0];
-    for (int i = 1; i < nw; ++i) bq += sm.q[i];
+  if (w == 0) {
+    const bool on = lane < (int)(blockDim.x / kWave);
     Partial p;
     p.n = 0;
     p.kmin = p.kmax = 0;
     p.s = 0.0;
-    p.q = bq;
+    p.q = wave_sum_f64(on ? sm.q[on ? lane : 0] : 0.0);
     p.si = 0;
     p.qi = 0;
-    *out = p;
+    if (lane == 0) *out = p;
   }
 }
 
@@ -757,15 +734,18 @@ TSA_DEV bool block_select_u32(const uint32_t* hist, int nb, uint64_t k, SH& sh, 
   const int per = (nb + bs - 1) / bs;
   const int b0 = t * per;
   uint64_t local = 0;
-  for (int i = 0; i < per; ++i)
-    if (b0 + i < nb) local += hist[b0 + i];
-  const int lane = t % kWave, w = t / kWave;
-  uint64_t inc = local;
+  if (per <= 8) {
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint64_t y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
+    for (int i = 0; i < 8; ++i) {  // every read in flight at once
+      const uint32_t h = hist[min(b0 + i, nb - 1)];
+      local += (i < per && b0 + i < nb) ? h : 0u;
+    }
+  } else {
+    for (int i = 0; i < per; ++i)
+      if (b0 + i < nb) local += hist[b0 + i];
   }
+  const int lane = t % kWave, w = t / kWave;
+  const uint64_t inc = wave_scan_incl_u64(local);
   if (lane == kWave - 1) sh.wsum[w] = inc;
   if (t == 0) sh.found = 0;
   __syncthreads();
@@ -825,7 +805,13 @@ TSA_DEV bool block_select_small(const uint32_t* hist, int nb, uint32_t k, SH& sh
   const int per = (nb + bs - 1) / bs;
   const int b0 = t * per;
   uint32_t local = 0;
-  if ((per & (per - 1)) == 0) {  // a power of two: each run read from an offset rotated by t / 8,
+  if (per <= 8 && (per & (per - 1)) != 0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {  // every read in flight at once
+      const uint32_t h = hist[at(min(b0 + i, nb - 1))];
+      local += (i < per && b0 + i < nb) ? h : 0u;
+    }
+  } else if ((per & (per - 1)) == 0) {  // a power of two: each run read from an offset rotated by t / 8,
     // so lanes whose runs start in the same bank read different banks (8 a run: none shared)
     for (int i = 0; i < per; ++i) {
       const int j = b0 + ((i + (t >> 3)) & (per - 1));
@@ -849,19 +835,35 @@ TSA_DEV bool block_select_small(const uint32_t* hist, int nb, uint32_t k, SH& sh
             (4 * i + 3 < w ? v.w : 0u);
   }
   if (local > 0 && k >= base && k - base < local) {
-    uint32_t cum = base;
+    uint32_t cum = base, in = 0;
     int d = b0;
-    for (int i = 0; i < per; ++i) {
-      const uint32_t h = (b0 + i < nb) ? hist[at(b0 + i)] : 0u;
-      if (k - cum < h) {
-        d = b0 + i;
-        break;
+    if (per <= 8) {
+      uint32_t h[8], below = base;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) h[i] = hist[at(min(b0 + i, nb - 1))];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t c = (i < per && b0 + i < nb) ? h[i] : 0u;
+        if (k >= below && k - below < c) {
+          d = b0 + i;
+          cum = below;
+          in = c;
+        }
+        below += c;
       }
-      cum += h;
+    } else {
+      for (int i = 0; i < per; ++i) {
+        in = (b0 + i < nb) ? hist[at(b0 + i)] : 0u;
+        if (k - cum < in) {
+          d = b0 + i;
+          break;
+        }
+        cum += in;
+      }
     }
     sh.sel_digit = (uint32_t)d;
     sh.sel_cum32 = cum;
-    sh.sel_bucket32 = hist[at(d)];
+    sh.sel_bucket32 = in;
     sh.found = 1;
   }
   __syncthreads();
