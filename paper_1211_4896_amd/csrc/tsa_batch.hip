@@ -807,10 +807,10 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
         lds_zero(lds, hsize + kBins2);
         __syncthreads();
         const bool hist_on = v.hist_ok != 0, var_on = DT == 0 && v.var_on != 0;
-        Pass2Acc<DT, HistOwnAcc> f{
+        Pass2Acc<DT, HistOwnAcc, true> f{
             HistOwnAcc(lds, v.lo, v.scale, a.nbins, a.rshift),
-            Level2Acc<DT>(l2, v.prefix, true, v.compact != 0,
-                          cand_sink(cs, a.pool + v.cand_base, &s.cand_fill, v.cand_n, true)),
+            Level2Acc<DT, true>(l2, v.prefix, true, v.compact != 0,
+                                cand_sink<true>(cs, a.pool + v.cand_base, &s.cand_fill, v.cand_n)),
             VarAcc{v.shift}, hist_on, true, var_on};
         walk_tile<DT, VEC, NT>(a, g, tile, f);
         f.l2.finish();

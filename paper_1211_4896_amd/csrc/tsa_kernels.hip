@@ -661,8 +661,9 @@ TSA_DEV void mid_tail(const Partial* parts, int np, int dtype, uint64_t volume, 
   }
 }
 
-// Bound by HBM: 1024x1024x1280 voxels (5.4 GB) 0.90 ms, 6.0 TB/s (0.91 without
-// the loads a chunk ahead; the same launch with only the loads takes 0.86).
+// Bound by HBM: 1024x1024x1280 voxels (5.4 GB) 0.86 ms, 6.2 TB/s, which a launch
+// with only the loads takes too (two blocks per compute unit; with three, or
+// with loads issued a chunk ahead, 0.89 to 0.91).
 template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_a(Geom g, uint32_t rshift, Partial* __restrict__ parts,
                                                  uint64_t* __restrict__ hist1, uint64_t* __restrict__ hcopy,
@@ -677,7 +678,7 @@ __global__ __launch_bounds__(1024) void k_pass_a(Geom g, uint32_t rshift, Partia
   lds_zero(lds, ((uint32_t)kBins1 << rshift) + kTrash);
   __syncthreads();
   Pass1Acc<DT> a(lds, rshift);
-  walk<DT, VEC, kUnrollOf<DT, VEC>, NT, DT == 0>(g, a);
+  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, a);
   // every valid value incremented one first-digit counter: the block's count
   // is their total (each lane adds a strided share; the partial sums them)
   __syncthreads();
@@ -740,7 +741,7 @@ __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t
   const bool var_on = DT == 0 && st->var_on != 0;
   if (!hist_on && !sel_on && !var_on) return;
   lds_zero(lds, hsize + kBins2);
-  const CandSink sink = cand_sink_lds(l2 + kBins2, stage, cand, &st->ncand, st->cand_cap);
+  const CandSink<> sink = cand_sink_lds(l2 + kBins2, stage, cand, &st->ncand, st->cand_cap);
   __syncthreads();
   Pass2Acc<DT, HistOwnAcc> b{HistOwnAcc(lds, st->lo, st->scale, nbins, rshift),
                              Level2Acc<DT>(l2, st->prefix, sel_on, st->compact != 0, sink), VarAcc{st->shift},
@@ -778,7 +779,7 @@ __global__ __launch_bounds__(1024) void k_pass_bwin(Geom g, int32_t nbins, SelSt
   const bool var_on = DT == 0 && st->var_on != 0;
   if (!hist_on && !sel_on && !var_on) return;
   lds_zero(lds, kWinBins + kBins2);
-  const CandSink sink = cand_sink_lds(l2 + kBins2, kWaveStage, cand, &st->ncand, st->cand_cap);
+  const CandSink<> sink = cand_sink_lds(l2 + kBins2, kWaveStage, cand, &st->ncand, st->cand_cap);
   __syncthreads();
   const int32_t w0 = st->win0;
   Pass2Acc<DT, HistWinAcc> b{HistWinAcc{lds, st->lo, st->scale, nbins - 1, w0, counts},
@@ -1156,13 +1157,10 @@ struct Prep {
 };
 
 // Blocks per compute unit by call: the histogram and radix passes lose by a
-// third, the moments gain.  The fused trio takes three on large regions (pass A
-// and B on 1024x1024x1280 float32 voxels: 895 + 916 us, with two 865 + 933,
-// and the shorter lane sums carry less rounding) and where rows are read one by
-// one (1711x1711x246 box: 561 + 617 against 595 + 673), two below kTrio3 voxels,
-// where each has little to do (400^3: 104 us with two, 112 with three).
+// third, the moments gain.  The fused trio takes three where rows are read one by
+// one (1711x1711x246 box: 561 + 617 us against 595 + 673), else two (1024x1024x1280
+// float32 voxels: 1.73 ms, with three 1.83; 400^3: 104 us, with three 112).
 constexpr int kBpcStats = 2, kBpcMoments = 3, kBpcHist = 2, kBpcSelect = 2;
-constexpr int64_t kTrio3 = 1ll << 28;
 
 static int prepare(const tsa_cube* cube, const tsa_region* region, void* d_ws, size_t ws_bytes,
                    tsa_stream_t stream, Prep* P, int bpc_default, int64_t cand_limit = INT64_MAX, bool trio = false) {
@@ -1178,7 +1176,7 @@ static int prepare(const tsa_cube* cube, const tsa_region* region, void* d_ws, s
   const Tuning& T = tuning();
   P->block = T.block;
   P->bpc = T.bpc ? T.bpc : bpc_default;
-  if (!T.bpc && trio && (P->volume >= kTrio3 || P->g.mode == 1)) P->bpc = 3;
+  if (!T.bpc && trio && P->g.mode == 1) P->bpc = 3;
   int maxb = P->dev.cus * P->bpc;
   if (maxb > kMaxBlocks) maxb = kMaxBlocks;
   P->grid = pass_grid(P->g, P->vec, P->block, maxb);
