@@ -246,7 +246,7 @@ def stats(t, nbins: int, region=None, stream=None):
     torch = _torch()
     c, reg = cube_of(t), region_of(region)
     ws = workspace(OP_STATS, t, region, nbins)
-    out = _result_buf(t)
+    out = torch.empty(72, dtype=torch.uint8, device=t.device)  # the call writes every field
     counts = torch.empty(nbins, dtype=torch.int64, device=t.device)
     outl = torch.empty(2, dtype=torch.int64, device=t.device)
     _check(capi().tsa_stats(ctypes.byref(c), _rp(reg), nbins, out.data_ptr(), counts.data_ptr(), outl.data_ptr(),
@@ -260,7 +260,7 @@ def stats_static(t, nbins: int, region=None, stream=None):
     per-device scratch instead.  Returns (result dict, counts, outliers)."""
     torch = _torch()
     c, reg = cube_of(t), region_of(region)
-    out = _result_buf(t)
+    out = torch.empty(72, dtype=torch.uint8, device=t.device)  # the call writes every field
     counts = torch.empty(nbins, dtype=torch.int64, device=t.device)
     outl = torch.empty(2, dtype=torch.int64, device=t.device)
     _check(capi().tsa_stats_static(ctypes.byref(c), _rp(reg), nbins, out.data_ptr(), counts.data_ptr(),

@@ -25,8 +25,8 @@ constexpr int kUnrollOf = DT == 1 && VEC == 2 ? 2 : kUnroll;
 constexpr uint32_t kTileUnits = 8192; // vectors per rows tile (single-region calls), at most
 constexpr int kMaxBlocks = 7936;      // upper bound of a pass grid (moment partial slots)
 // The fused passes add their per-block counts into kHistCopies copies of a
-// histogram (block b into copy b % kHistCopies), summed by the next one-block
-// kernel: a thousand blocks ending together otherwise queue on the same
+// histogram (block b into copy b % kHistCopies), summed by pass A's last block
+// and by the launch after pass B: a thousand blocks ending together otherwise queue on the same
 // counters.  Pass B's copies hold up to kCopyBinsMax bins (more bins take the
 // wide passes, which count into the output directly).
 constexpr int kHistCopies = 8;

@@ -375,7 +375,7 @@ __global__ __launch_bounds__(1024) void k_level3(Geom g, SelState* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// one-block epilogues: moments merge and digit selection
+// epilogues of one block: moments merge and digit selection
 // ---------------------------------------------------------------------------
 
 // Per-thread arrays of a block's merge (32 bytes a thread).
