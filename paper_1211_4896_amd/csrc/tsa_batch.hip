@@ -53,7 +53,7 @@ struct QState {
   uint32_t done1, done2, done3;
   uint32_t p1_ready, p2_ready;
   uint32_t skip2, need3, compact, cand_base, cand_n, cand_fill;
-  uint32_t prefix, hist_ok, var_on, finished;
+  uint32_t prefix, hist_ok, var_on, pad;
   float lo, hi, scale, shift;
   uint64_t n, k;
 };
@@ -201,7 +201,8 @@ __global__ void k_bplan(BArgs a) {
       g.vpr_m = dev_magic(g.vpr);
       g.valid = ok ? 1u : 0u;
       g.solo = (ok && nt == 1) ? 1u : 0u;
-      res.nan_count = vol;  // until the moments say otherwise
+      res.nan_count = vol;        // until the moments say otherwise
+      res.status = TSA_EDEVICE;  // until the box is finished (a bounded wait may give up before)
     }
   }
   if (!ok) {
@@ -384,7 +385,7 @@ TSA_DEV void epilogue1(const BArgs& a, uint32_t q, BShared& sh, uint32_t* lds) {
     s.n = cnt;
     if (cnt == 0) {
       R.flags |= TSA_FLAG_HIST_SKIPPED;
-      s.finished = 1;
+      R.status = TSA_OK;
     } else {
       const double vmin = bvalue_of_key(kmin, DT), vmax = bvalue_of_key(kmax, DT);
       R.min = vmin;
@@ -398,7 +399,7 @@ TSA_DEV void epilogue1(const BArgs& a, uint32_t q, BShared& sh, uint32_t* lds) {
           a.hists[(size_t)q * a.nbins] = cnt;  // lo == hi: every value in bin 0
         else
           R.flags |= TSA_FLAG_HIST_SKIPPED;  // an infinite range has no bins
-        s.finished = 1;
+        R.status = TSA_OK;
       } else {
         const double q2 = ep.mq[0] < 0.0 ? 0.0 : ep.mq[0];  // NaN (infinite values) stays
         R.mean = mean;
@@ -418,7 +419,6 @@ TSA_DEV void epilogue1(const BArgs& a, uint32_t q, BShared& sh, uint32_t* lds) {
       if (!found) {
         R.status = TSA_EDEVICE;
         skip2 = true;
-        s.finished = 1;
       } else {
         s.prefix = d << kShift1;
         s.k = k - cum;
@@ -492,14 +492,11 @@ TSA_DEV void epilogue2(const BArgs& a, uint32_t q, BShared& sh, uint32_t* lds) {
     const uint32_t prefix = s.prefix | (d << kShift2);
     const uint32_t k2 = (uint32_t)s.k - cum;
     if (!found) {
-      if (t == 0) {
-        R.status = TSA_EDEVICE;
-        s.finished = 1;
-      }
+      if (t == 0) R.status = TSA_EDEVICE;
     } else if (DT == 1) {  // int16 keys have no bits below the second digit
       if (t == 0) {
         R.median = bvalue_of_key(prefix, DT);
-        s.finished = 1;
+        R.status = TSA_OK;
       }
     } else if (s.compact) {
       // last 8 bits from the copied candidates
@@ -516,11 +513,8 @@ TSA_DEV void epilogue2(const BArgs& a, uint32_t q, BShared& sh, uint32_t* lds) {
       uint32_t d3, cum3, b3;
       found = block_select_small(lds, kBins3, k2, sh, &d3, &cum3, &b3);
       if (t == 0) {
-        if (found)
-          R.median = bvalue_of_key(prefix | d3, DT);
-        else
-          R.status = TSA_EDEVICE;
-        s.finished = 1;
+        if (found) R.median = bvalue_of_key(prefix | d3, DT);
+        R.status = found ? TSA_OK : TSA_EDEVICE;
       }
     } else {
       for (int i = t; i < kBins3; i += bs) dig[i] = 0u;
@@ -545,11 +539,8 @@ TSA_DEV void epilogue3(const BArgs& a, uint32_t q, BShared& sh) {
   uint32_t d, cum, bucket;
   const bool found = block_select_small(a.digits + (size_t)q * kBins1, kBins3, (uint32_t)s.k, sh, &d, &cum, &bucket);
   if (threadIdx.x == 0) {
-    if (found)
-      a.results[q].median = bvalue_of_key(s.prefix | d, DT);
-    else
-      a.results[q].status = TSA_EDEVICE;
-    s.finished = 1;
+    if (found) a.results[q].median = bvalue_of_key(s.prefix | d, DT);
+    a.results[q].status = found ? TSA_OK : TSA_EDEVICE;
   }
   __syncthreads();
 }
@@ -621,16 +612,13 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
     }
   }
   if (cnt == 0 || kmin == kmax) {
-    if (t == 0) s.finished = 1;
+    if (t == 0) R.status = TSA_OK;
     return;
   }
   const uint32_t k = (uint32_t)((cnt - 1) / 2);  // a box holds fewer than 2^32 voxels
   uint32_t d, cum, bucket;
   if (!block_select_small(lds, kBins1, k, sh, &d, &cum, &bucket, [](uint32_t i) { return digit_slot<DT>(i); })) {
-    if (t == 0) {
-      R.status = TSA_EDEVICE;
-      s.finished = 1;
-    }
+    if (t == 0) R.status = TSA_EDEVICE;
     return;
   }
   const uint32_t prefix = d << kShift1;
@@ -692,10 +680,7 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
   }
   uint32_t d2, cum2, b2;
   if (!block_select_small(l2, kBins2, k2, sh, &d2, &cum2, &b2)) {  // ends with a barrier
-    if (t == 0) {
-      R.status = TSA_EDEVICE;
-      s.finished = 1;
-    }
+    if (t == 0) R.status = TSA_EDEVICE;
     return;
   }
   const uint32_t prefix2 = prefix | (d2 << kShift2);
@@ -703,7 +688,7 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
   if (DT == 1) {  // int16 keys have no bits below the second digit
     if (t == 0) {
       R.median = bvalue_of_key(prefix2, DT);
-      s.finished = 1;
+      R.status = TSA_OK;
     }
     return;
   }
@@ -727,11 +712,8 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
   uint32_t d3, cum3, b3;
   const bool found = block_select_small(lds, kBins3, k3, sh, &d3, &cum3, &b3);
   if (t == 0) {
-    if (found)
-      R.median = bvalue_of_key(prefix2 | d3, DT);
-    else
-      R.status = TSA_EDEVICE;
-    s.finished = 1;
+    if (found) R.median = bvalue_of_key(prefix2 | d3, DT);
+    R.status = found ? TSA_OK : TSA_EDEVICE;
   }
 }
 
@@ -882,13 +864,6 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
     }
     __syncthreads();
   }
-}
-
-// Boxes left unfinished (a bounded wait gave up) report a device error.
-__global__ void k_bfinal(BArgs a) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= a.nq) return;
-  if (a.geom[q].valid && !a.st[q].finished) a.results[q].status = TSA_EDEVICE;
 }
 
 // ---------------------------------------------------------------------------
@@ -1209,7 +1184,6 @@ static int enqueue_region_batch(const tsa_cube* cube, const tsa_region* d_region
       TSA_BATCH_LAUNCH(1, 0, false);
   }
 #undef TSA_BATCH_LAUNCH
-  TSA_TRACED("batch_final", s, hipLaunchKernelGGL(k_bfinal, dim3(pb), dim3(256), 0, s, a));
   return hipGetLastError() == hipSuccess ? TSA_OK : TSA_EDEVICE;
 }
 
