@@ -113,8 +113,9 @@ struct BArgs {
 // the per-tile zeroing, flushing and counting rare.
 constexpr uint32_t kAutoMinVoxels = 16384, kAutoMaxVoxels = 1u << 20;
 
+// (One block.)
 template <int DT>
-__global__ __launch_bounds__(1024) void k_bauto(BArgs a) {
+TSA_DEV void choose_tiles(const BArgs& a) {
   __shared__ uint64_t part[16];
   const int t = threadIdx.x;
   const int64_t epv = DT == 0 ? 4 : 8;
@@ -145,9 +146,7 @@ __global__ __launch_bounds__(1024) void k_bauto(BArgs a) {
 }
 
 template <int DT>
-__global__ void k_bplan(BArgs a) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= a.nq) return;
+TSA_DEV void plan_box(const BArgs& a, int q) {
   const tsa_region r = a.regions[q];
   QGeom g;
   memset(&g, 0, sizeof(g));
@@ -219,7 +218,7 @@ __global__ void k_bplan(BArgs a) {
 }
 
 // Exclusive scan of the tile counts (one block) and the batch header.
-__global__ __launch_bounds__(1024) void k_bscan(BArgs a) {
+TSA_DEV void scan_tiles(const BArgs& a) {
   __shared__ uint64_t wsum[16];
   const int t = threadIdx.x, bs = blockDim.x;
   const int per = (a.nq + bs - 1) / bs;
@@ -228,12 +227,7 @@ __global__ __launch_bounds__(1024) void k_bscan(BArgs a) {
   for (int i = 0; i < per; ++i)
     if (q0 + i < a.nq) local += a.geom[q0 + i].ntiles;
   const int lane = t % kWave, w = t / kWave;
-  uint64_t inc = local;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint64_t y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
-  }
+  const uint64_t inc = wave_scan_incl_u64(local);
   if (lane == kWave - 1) wsum[w] = inc;
   __syncthreads();
   uint64_t base = inc - local, total = 0;
@@ -254,6 +248,29 @@ __global__ __launch_bounds__(1024) void k_bscan(BArgs a) {
     a.hdr->T1 = total;
     a.hdr->nq = (uint32_t)a.nq;
   }
+}
+
+template <int DT>
+__global__ __launch_bounds__(1024) void k_bauto(BArgs a) {
+  choose_tiles<DT>(a);
+}
+template <int DT>
+__global__ void k_bplan(BArgs a) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q < a.nq) plan_box<DT>(a, q);
+}
+__global__ __launch_bounds__(1024) void k_bscan(BArgs a) { scan_tiles(a); }
+
+// The three together for batches of at most a box a thread: each thread scans
+// the box that it planned, so the steps meet at barriers of one block instead
+// of at launches (each 3 to 4 us, of 78 for 64 small boxes).
+constexpr int kSetupBoxes = 1024;
+template <int DT>
+__global__ __launch_bounds__(kSetupBoxes) void k_bsetup(BArgs a) {
+  if (!a.tile_units) choose_tiles<DT>(a);
+  __syncthreads();  // the tile size that thread 0 wrote
+  if ((int)threadIdx.x < a.nq) plan_box<DT>(a, (int)threadIdx.x);
+  scan_tiles(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1153,18 +1170,26 @@ static int enqueue_region_batch(const tsa_cube* cube, const tsa_region* d_region
   size_t lds = lds1 > lds2 ? lds1 : lds2;
   if (lds < kEpLdsBytes) lds = kEpLdsBytes;
   bfill3(a.hdr, sizeof(BatchHdr) / 4, a.digits, (size_t)kBins1 * nq, d_hists, (size_t)nbins * nq * 2, s);
-  const int pb = (nq + 255) / 256;
-  if (!a.tile_units) {
-    if (cube->dtype == TSA_F32)
-      TSA_TRACED("batch_auto", s, hipLaunchKernelGGL(k_bauto<0>, dim3(1), dim3(1024), 0, s, a));
+  const bool f32 = cube->dtype == TSA_F32;
+  if (nq <= kSetupBoxes) {
+    if (f32)
+      TSA_TRACED("batch_plan", s, hipLaunchKernelGGL(k_bsetup<0>, dim3(1), dim3(kSetupBoxes), 0, s, a));
     else
-      TSA_TRACED("batch_auto", s, hipLaunchKernelGGL(k_bauto<1>, dim3(1), dim3(1024), 0, s, a));
+      TSA_TRACED("batch_plan", s, hipLaunchKernelGGL(k_bsetup<1>, dim3(1), dim3(kSetupBoxes), 0, s, a));
+  } else {
+    const int pb = (nq + 255) / 256;
+    if (!a.tile_units) {
+      if (f32)
+        TSA_TRACED("batch_auto", s, hipLaunchKernelGGL(k_bauto<0>, dim3(1), dim3(1024), 0, s, a));
+      else
+        TSA_TRACED("batch_auto", s, hipLaunchKernelGGL(k_bauto<1>, dim3(1), dim3(1024), 0, s, a));
+    }
+    if (f32)
+      TSA_TRACED("batch_plan", s, hipLaunchKernelGGL(k_bplan<0>, dim3(pb), dim3(256), 0, s, a));
+    else
+      TSA_TRACED("batch_plan", s, hipLaunchKernelGGL(k_bplan<1>, dim3(pb), dim3(256), 0, s, a));
+    TSA_TRACED("batch_scan", s, hipLaunchKernelGGL(k_bscan, dim3(1), dim3(1024), 0, s, a));
   }
-  if (cube->dtype == TSA_F32)
-    TSA_TRACED("batch_plan", s, hipLaunchKernelGGL(k_bplan<0>, dim3(pb), dim3(256), 0, s, a));
-  else
-    TSA_TRACED("batch_plan", s, hipLaunchKernelGGL(k_bplan<1>, dim3(pb), dim3(256), 0, s, a));
-  TSA_TRACED("batch_scan", s, hipLaunchKernelGGL(k_bscan, dim3(1), dim3(1024), 0, s, a));
   const int grid = (int)a.grid;
 #define TSA_BATCH_LAUNCH(D, V, N) \
   TSA_TRACED("batch", s, hipLaunchKernelGGL((k_batch<D, V, N>), dim3(grid), dim3(kBBlock), lds, s, a))
