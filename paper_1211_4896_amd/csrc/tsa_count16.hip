@@ -106,10 +106,26 @@ __global__ __launch_bounds__(kCountThreads) void k_count16(Geom g, uint32_t* __r
   }
 }
 
-// Sums of one group of kGroup keys.  v^2 c is split at 2^20 of c, so neither
-// part leaves 64 bits for cubes below 2^46 voxels.
+// The sum of v^2 over voxels as high 2^20 + low.  One value's count c is split
+// at 2^20, so its parts are below 2^50 and (c < 2^46) 2^56, and the low parts of
+// a group of 1024 values sum to less than 2^60; all 65536 values' would not fit
+// 64 bits, so each group's low part is carried into its high part before groups
+// are added.  The high part of everything is below 2^30 2^46 / 2^20.
+struct Squares {
+  uint64_t low, high;
+};
+__host__ __device__ __forceinline__ Squares squares_of(int64_t v, uint64_t c) {
+  const uint64_t v2 = (uint64_t)(v * v);
+  return Squares{v2 * (c & 0xFFFFFull), v2 * (c >> 20)};
+}
+__host__ __device__ __forceinline__ Squares carried(const Squares& q) {
+  return Squares{q.low & 0xFFFFFull, q.high + (q.low >> 20)};
+}
+
+// Sums of one group of kGroup keys.
 struct Group16 {
-  uint64_t n, q0, q1;
+  uint64_t n;
+  Squares q;  // carried
   int64_t s;
   uint32_t kmin, kmax;  // keys that occur (kmin > kmax: none)
   uint64_t pad;
@@ -166,9 +182,9 @@ __global__ __launch_bounds__(kGroup) void k_reduce16(const uint32_t* __restrict_
   uint64_t tot;
   adj_loc[key] = block_prefix_u64(c, wsum, &tot);  // every thread read only its own entry
   const int64_t v = (int64_t)key - 32768;
-  const uint64_t v2 = (uint64_t)(v * v);
+  const Squares q = squares_of(v, c);
   const int64_t s = wave_sum_i64(v * (int64_t)c);
-  const uint64_t q0 = wave_sum_u64(v2 * (c & 0xFFFFFull)), q1 = wave_sum_u64(v2 * (c >> 20));
+  const uint64_t q0 = wave_sum_u64(q.low), q1 = wave_sum_u64(q.high);
   const uint32_t mn = wave_min_u32(c ? key : 0xFFFFFFFFu), mx = wave_max_u32(c ? key : 0u);
   if (t % kWave == 0) {
     const uint32_t w = t / kWave;
@@ -180,14 +196,15 @@ __global__ __launch_bounds__(kGroup) void k_reduce16(const uint32_t* __restrict_
   }
   __syncthreads();
   if (t == 0) {
-    Group16 G{tot, 0, 0, 0, 0xFFFFFFFFu, 0u, 0};
+    Group16 G{tot, {0, 0}, 0, 0xFFFFFFFFu, 0u, 0};
     for (int w = 0; w < 16; ++w) {
       G.s += ss[w];
-      G.q0 += sq0[w];
-      G.q1 += sq1[w];
+      G.q.low += sq0[w];
+      G.q.high += sq1[w];
       G.kmin = min(G.kmin, smn[w]);
       G.kmax = max(G.kmax, smx[w]);
     }
+    G.q = carried(G.q);
     groups[blockIdx.x] = G;
   }
 }
@@ -227,12 +244,19 @@ TSA_DEV uint32_t wave_search(uint32_t n, F f) {
 }
 
 // x rounded once to double.
-TSA_DEV double u128_to_f64(unsigned __int128 x) {
+__host__ __device__ __forceinline__ double u128_to_f64(unsigned __int128 x) {
   const uint64_t hi = (uint64_t)(x >> 64);
   if (!hi) return (double)(uint64_t)x;
   const int sh = 64 - __builtin_clzll(hi);  // bits below the leading 64, kept as a sticky bit
   const uint64_t sticky = (uint64_t)x << (64 - sh) ? 1u : 0u;
   return ldexp((double)((uint64_t)(x >> sh) | sticky), sh);
+}
+
+// M2 of n voxels of sum S and sum of squares q: n Q - S^2 >= 0 in 128 bits
+// (n <= 2^46, Q <= 2^76, |S| <= 2^61).
+__host__ __device__ __forceinline__ double m2_of_sums(uint64_t n, int64_t S, const Squares& q) {
+  const unsigned __int128 Q = ((unsigned __int128)q.high << 20) + q.low;
+  return u128_to_f64(Q * n - (unsigned __int128)((__int128)S * S)) / (double)n;
 }
 
 // The scalar answers, by one wave.
@@ -251,7 +275,7 @@ __global__ __launch_bounds__(kWave) void k_fin16(const Group16* __restrict__ gro
   base[t] = inc - g.n;
   if (t == kWave - 1) base[kGroups] = inc;
   const int64_t S = wave_sum_i64(g.s);
-  const uint64_t q0 = wave_sum_u64(g.q0), q1 = wave_sum_u64(g.q1);
+  const Squares q{wave_sum_u64(g.q.low), wave_sum_u64(g.q.high)};
   const uint32_t kmin = wave_min_u32(g.kmin), kmax = wave_max_u32(g.kmax);
   __syncthreads();
   const uint64_t n = __shfl(inc, kWave - 1);  // the region's volume: at least 1
@@ -275,9 +299,7 @@ __global__ __launch_bounds__(kWave) void k_fin16(const Group16* __restrict__ gro
         R->mean = (double)lo;
         R->m2 = R->std = 0.0;
       } else {
-        // n Q - S^2 >= 0 in 128 bits (n < 2^47, Q < 2^77, |S| < 2^62)
-        const unsigned __int128 Q = ((unsigned __int128)q1 << 20) + q0;
-        const double m2 = u128_to_f64(Q * n - (unsigned __int128)((__int128)S * S)) / (double)n;
+        const double m2 = m2_of_sums(n, S, q);
         R->mean = (double)S / (double)n;
         R->m2 = m2;
         R->std = sqrt(m2 / (double)n);
@@ -419,3 +441,30 @@ int run_count16(const Geom& g, int vec, int grid, int mode, void* scratch, void*
 }
 
 }  // namespace tsa
+
+// The moments the count gives, from the counts of the 65536 values (by key, value
+// + 32768), summed on the host as the kernels sum them: a group of values at a
+// time, then the groups.
+extern "C" void tsa_internal_moments16(const uint64_t* counts, uint64_t* n, double* mean, double* m2) {
+  using namespace tsa;
+  uint64_t N = 0;
+  int64_t S = 0;
+  Squares q{0, 0};
+  for (uint32_t g = 0; g < kGroups; ++g) {
+    Squares gq{0, 0};
+    for (uint32_t key = g * kGroup; key < (g + 1) * kGroup; ++key) {
+      const int64_t v = (int64_t)key - 32768;
+      const Squares x = squares_of(v, counts[key]);
+      N += counts[key];
+      S += v * (int64_t)counts[key];
+      gq.low += x.low;
+      gq.high += x.high;
+    }
+    gq = carried(gq);
+    q.low += gq.low;
+    q.high += gq.high;
+  }
+  *n = N;
+  *mean = (double)S / (double)N;
+  *m2 = m2_of_sums(N, S, q);
+}
