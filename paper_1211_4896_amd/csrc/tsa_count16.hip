@@ -16,7 +16,7 @@
 //
 // Bound: HBM reads (6.25 TB/s).  2048^3 voxels (17.2 GB), all three statistics:
 // 7.64 ms in two passes that the vector ALU bounded (17 operations a voxel
-// each, lane masks spilled) -> 2.78 ms, 2.74 ms of it the count.
+// each, lane masks spilled) -> 2.66 ms.  One value in 2^29 voxels: 3.1 ms -> 0.26.
 #include <math.h>
 
 #include "tsa_internal.hpp"
@@ -39,20 +39,44 @@ TSA_DEV uint32_t pk_max(uint32_t a, uint32_t b) {
 }
 TSA_DEV bool half_full(uint32_t m) { return (m & 0xFFFFu) == 0xFFFFu || m >= 0xFFFF0000u; }
 
-// One 16-byte vector costs 5 VALU operations and one LDS increment a voxel.
+// One 16-byte vector costs 5 VALU operations and one LDS increment a voxel.  A
+// lane whose eight voxels are equal adds 8 at once: in runs of one value (sorted
+// data, blanked parts) a wave's lanes meet on few words, and each increment of a
+// shared word waits for the one before.
 struct Count16Acc {
   uint32_t base;  // LDS byte address of the words
   uint64_t* adj;  // by key: what the wraps add (mod 2^64)
   // the increment `inc` of the word at byte offset `at` found `old`
   TSA_DEV void wrapped(uint32_t at, uint32_t inc, uint32_t old) {
     const uint32_t i = at >> 2;  // the high half's key; the low half's is i + 32768
-    if (inc == 1u && (old & 0xFFFFu) == 0xFFFFu) {  // the low half wrapped into the high one
+    if ((old & 0xFFFFu) + (inc & 0xFFFFu) > 0xFFFFu) {  // the low half wrapped into the high one
       atomicAdd((unsigned long long*)(adj + kWords + i), 65536ull);
       atomicAdd((unsigned long long*)(adj + i), ~0ull);
     }
     if (old + inc < old) atomicAdd((unsigned long long*)(adj + i), 65536ull);  // the word wrapped
   }
+  // whether some lane of the wave may hold eight equal voxels (none does in most waves of noise)
+  TSA_DEV static bool may_run(const uint4& r) { return __ballot(r.x == r.w) != 0ull; }
+  // The vectors of a chunk: one test for all of them (a test each: 2660 -> 2715 us over 2048^3 voxels).
+  template <int U>
+  TSA_DEV void vecs(const uint4 (&r)[U]) {
+    if (may_run(r[0])) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) vec(r[u]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) singles(r[u]);
+    }
+  }
   TSA_DEV void vec(const uint4& r) {
+    if (may_run(r) && r.x == r.w && r.x == r.y && r.x == r.z && r.x >> 16 == (r.x & 0xFFFFu)) {
+      const uint32_t at = (r.x << 2) & 0x1FFFCu, inc = (r.x & 0x8000u) ? 0x80000u : 8u;
+      wrapped(at, inc, lds_add_rtn(base + at, inc));
+    } else {
+      singles(r);
+    }
+  }
+  TSA_DEV void singles(const uint4& r) {
     const uint32_t w[4] = {r.x, r.y, r.z, r.w};
     uint32_t at[8], inc[8], old[8];
 #pragma unroll
@@ -377,18 +401,19 @@ __global__ void k_clear16(uint64_t* __restrict__ p, uint32_t n) {
 // The least voxels of a region, by call, and of a block.  A block's counts
 // leave it as up to 32768 additions to global memory (186 G/s over the chip:
 // 45 us from 256 blocks of evenly spread values), so below 2^25 voxels fewer
-// blocks of 2^17 voxels each are launched, and a call takes this path from
-// the size where it wins for every distribution tried (evenly spread, noise
-// of 300 and of 3 counts, one value).  us, key digits -> counts:
-//   stats    2^24: spread 92 -> 59, noise 80 -> 39, one value 159 -> 137 (2^23: 97 -> 136)
-//   MAD      2^23: spread 101 -> 36, noise 97 -> 26, one value 171 -> 128 (2^22: 117 -> 127)
-//   median   2^28: spread 180 -> 134, noise 181 -> 99, one value 1346 -> 900 (2^26: spread 69 -> 85)
+// blocks of 2^17 voxels each are launched.  Ranks take this path from the size
+// where it wins for every distribution tried (evenly spread, noise of 300 and of 3
+// counts, one value); the others win at half their least sizes too.  us, key
+// digits -> counts:
+//   stats    2^24: spread 90 -> 58, noise 80 -> 38, one value 159 -> 40 (2^23: 69 -> 45, 61 -> 36, 97 -> 38)
+//   MAD      2^23: spread 100 -> 35, noise 97 -> 25, one value 171 -> 30 (2^22: 80 -> 29, 76 -> 24, 117 -> 29)
+//   median   2^27: spread 103 -> 100, noise 106 -> 59, one value 685 -> 74 (2^26: spread 69 -> 83)
 // A quantile that stops after one digit stays with the digits: one pass either
-// way, and the count is the longer one (2^27 voxels: spread 61 -> 99, one value
-// 240 -> 458; 2^29: spread 177 -> 192, noise 182 -> 192, one value 902 -> 1797).
+// way, and the count is the longer one for spread values (2^27 voxels 57 -> 100, one
+// value 236 -> 74; 2^29: spread 172 -> 192, noise 182 -> 192).
 // The caller's-range histogram stays with its replicated bins: one pass either
-// way, and one value in every voxel takes 930 us there against 3560 us here
-// (2^30 voxels).
+// way (2^30 voxels, spread: 372 there, 352 here), and values that crowd on few
+// words in random order are slow without replicas (two values: 699 there, 2054 here).
 constexpr int64_t kCount16Stats = 1ll << 24, kCount16Mad = 1ll << 23, kCount16Rank = 1ll << 27;
 constexpr int64_t kCount16Block = 1ll << 17;
 

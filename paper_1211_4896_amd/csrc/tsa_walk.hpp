@@ -75,6 +75,22 @@ TSA_DEV void visit_vec(const uint4& r, F& f) {
   }
 }
 
+// The vectors of a chunk: f.vecs where the accumulator has it, else one by one.
+template <class F, int U, class = void>
+struct TakesVecs : std::false_type {};
+template <class F, int U>
+struct TakesVecs<F, U, std::void_t<decltype(std::declval<F&>().vecs(std::declval<const uint4 (&)[U]>()))>>
+    : std::true_type {};
+template <int DT, int U, class F>
+TSA_DEV void visit_vecs(const uint4 (&r)[U], F& f) {
+  if constexpr (TakesVecs<F, U>::value) {
+    f.vecs(r);
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; ++u) visit_vec<DT>(r[u], f);
+  }
+}
+
 // What an empty slot holds.
 constexpr uint32_t kNaNBits = 0x7FC00000u;
 template <int DT>
@@ -279,8 +295,7 @@ TSA_DEV void walk(const Geom& g, F& f) {
       };
       auto consume = [&](int64_t cb, const uint4(&r)[U]) {
         if (DT == 0 || cb + chunk <= g.v1) {
-#pragma unroll
-          for (int u = 0; u < U; ++u) visit_vec<DT>(r[u], f);
+          visit_vecs<DT>(r, f);
         } else {
 #pragma unroll
           for (int u = 0; u < U; ++u)
