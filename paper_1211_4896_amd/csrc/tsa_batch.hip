@@ -679,7 +679,7 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
   walk_tile<DT, VEC, NT>(a, g, 0u, f2);
   f2.l2.finish();
   __syncthreads();
-  if (hist_on) lds_flush_hist(lds, (uint32_t)a.nbins, a.rshift, a.hists + (size_t)q * a.nbins);
+  if (hist_on) lds_flush(lds, (uint32_t)a.nbins, a.rshift, a.hists + (size_t)q * a.nbins);
   if (var_on) {
     const double vq = wave_sum_f64(f2.var.q);
     const int w = t / kWave, lane = t % kWave;
@@ -814,7 +814,7 @@ __global__ __launch_bounds__(kBBlock) void k_batch(BArgs a) {
         walk_tile<DT, VEC, NT>(a, g, tile, f);
         f.l2.finish();
         __syncthreads();
-        if (hist_on) lds_flush_hist(lds, (uint32_t)a.nbins, a.rshift, a.hists + (size_t)q * a.nbins);
+        if (hist_on) lds_flush(lds, (uint32_t)a.nbins, a.rshift, a.hists + (size_t)q * a.nbins);
         uint32_t* dig = a.digits + (size_t)q * kBins1;
         for (int b = t; b < kBins2; b += kBBlock) {
           const uint32_t c = l2[b];

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(1024) void k_hist(Geom g, float lo, float hi, float
   HistAcc<DT> h(lds, lo, hi, scale, nbins, rshift);
   walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, h);
   __syncthreads();
-  lds_flush_hist(lds, (uint32_t)nbins, rshift, counts);
+  lds_flush(lds, (uint32_t)nbins, rshift, counts);
   block_add_outliers(h.below, h.above, outl, osm);
 }
 
@@ -751,7 +751,7 @@ __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t
   __syncthreads();
   // into one of kHistCopies copies (counts holds them nbins apart), summed by k_level3
   if (hist_on)
-    lds_flush_hist(lds, (uint32_t)nbins, rshift, counts + (size_t)(blockIdx.x % kHistCopies) * (uint32_t)nbins);
+    lds_flush(lds, (uint32_t)nbins, rshift, counts + (size_t)(blockIdx.x % kHistCopies) * (uint32_t)nbins);
   if (sel_on) lds_flush(l2, kBins2, 0, hist2);
   // values lie in their own [min, max]: the outlier counters keep their zeros
   if (var_on) {

@@ -475,20 +475,12 @@ TSA_DEV void lds_flush(const uint32_t* lds, uint32_t nbins, uint32_t rshift, uin
   }
 }
 
-// As lds_flush for a histogram whose vectors count the formula's t == nbins
-// (the value hi, rounded up) in a bin past the last instead of taking the
-// minimum for every value: that bin is the last one's.
-TSA_DEV void lds_flush_hist(const uint32_t* lds, uint32_t nbins, uint32_t rshift, uint64_t* g) {
-  const uint32_t R = 1u << rshift;
-  for (uint32_t b = threadIdx.x; b < nbins; b += blockDim.x) {
-    uint32_t c = 0;
-    for (uint32_t r = 0; r < (b + 1 == nbins ? 2 * R : R); ++r) c += lds[(b << rshift) + r];
-    if (c) atomicAdd((unsigned long long*)(g + b), (unsigned long long)c);
-  }
-}
-
 // ---- histogram (Section 4.1) ---------------------------------------------------
-// LDS: (nbins << rshift) + kTrash words (the bin past the last lies in the spare words).
+// LDS: (nbins << rshift) + kTrash words.  The vectors take the formula's minimum
+// value by value: it costs no time (1024x1024x1280 voxels with it 1723 us, without
+// 1726), and counting t == nbins past the last bin instead lengthens every flush
+// (10000 bins of 8^3 voxels 7.8 -> 9.1 us) and puts the extremes of two-valued data
+// into one LDS bank (640^3 voxels, 4096 bins: 1670 -> 1820 us).
 template <int DT>
 struct HistAcc {
   uint32_t* lds;
@@ -513,7 +505,7 @@ struct HistAcc {
     if (__ballot(!in) == 0ull) {
 #pragma unroll
       for (int e = 0; e < N; ++e)
-        lds_add_at(((uint32_t)(int32_t)((v[e] - lo) * scale) << (rshift + 2u)) + base, one);
+        lds_add_at(((uint32_t)min((int32_t)((v[e] - lo) * scale), nbm1) << (rshift + 2u)) + base, one);
     } else {
 #pragma unroll
       for (int e = 0; e < N; ++e) (*this)(v[e], true);
@@ -556,10 +548,10 @@ struct HistOwnAcc {
       lds_inc(lds, ((uint32_t)b << rshift) + rep);
     }
   }
-  TSA_DEV void four(const Four& f) {  // none of them NaN; t == nbins goes past the last bin (lds_flush_hist)
+  TSA_DEV void four(const Four& f) {  // none of them NaN
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      lds_add_at(((uint32_t)(int32_t)((f.v[e] - lo) * scale) << (rshift + 2u)) + base, one);
+      lds_add_at(((uint32_t)min((int32_t)((f.v[e] - lo) * scale), nbm1) << (rshift + 2u)) + base, one);
   }
   TSA_DEV void chunk() {}
 };
