@@ -26,7 +26,7 @@ namespace {
 
 constexpr uint32_t kVals = 65536, kWords = 32768;
 constexpr uint32_t kGroup = 1024, kGroups = kVals / kGroup;
-constexpr int kCountThreads = 1024;
+constexpr int kCountThreads = kCount16Step / kUnroll;
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 

@@ -74,7 +74,7 @@ int graph_run(const GraphKey& key, hipStream_t s, int (*enqueue)(void* ctx, hipS
 Magic make_magic(uint32_t d);
 int check_cube(const tsa_cube* c);
 int region_box(const tsa_cube* c, const tsa_region* r, tsa_region* b);
-int make_geom(const tsa_cube* c, const tsa_region& b, uint32_t tile_units, Geom* g, int* vec, int64_t* volume);
+int make_geom(const tsa_cube* c, const tsa_region& b, int cus, Geom* g, int* vec, int64_t* volume);
 // How the rows of boxes inside the cube are read (the walkers' VEC).
 int row_mode(const tsa_cube* c);
 size_t single_ws_bytes(int64_t volume);
@@ -91,6 +91,7 @@ struct Count16Ask {
   int32_t digits, mad, write_counts;
   double q;
 };
+constexpr uint32_t kCount16Step = 1024 * kUnroll;  // vectors that a block of the count takes at a time
 size_t count16_scratch_bytes();
 size_t count16_small_bytes();
 int count16_grid(int64_t volume, int blocks);
