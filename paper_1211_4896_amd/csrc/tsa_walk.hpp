@@ -117,7 +117,12 @@ TSA_DEV uint4 load16_any(const typename Ty<DT>::T* p) {
     v = *q;
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-// The first n (fewer than a vector's) elements from p, the rest empty.
+// The first n (1 to a vector's less one) elements from p.  float32: the rest empty.
+// int16: any values past n; four and more by two loads of four that overlap
+// in the row, two and three by two of two (an element a load: moments of
+// 7x250x250 voxels 12.2 -> 10.4 us).
+typedef uint64_t u64_any __attribute__((aligned(2)));
+typedef uint32_t u32_any __attribute__((aligned(2)));
 template <int DT>
 TSA_DEV uint4 load_narrow(const typename Ty<DT>::T* p, uint32_t n) {
   uint4 r = no_vec<DT>();
@@ -125,12 +130,14 @@ TSA_DEV uint4 load_narrow(const typename Ty<DT>::T* p, uint32_t n) {
     if (n > 0) r.x = __float_as_uint(p[0]);
     if (n > 1) r.y = __float_as_uint(p[1]);
     if (n > 2) r.z = __float_as_uint(p[2]);
+  } else if (n >= 4) {
+    const uint64_t a = *(const u64_any*)p, b = *(const u64_any*)(p + (n - 4)) >> (16 * (8 - n) & 63);
+    r = make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
+  } else if (n >= 2) {
+    r.x = *(const u32_any*)p;
+    r.y = *(const u32_any*)(p + (n - 2)) >> (16 * (4 - n) & 31);
   } else {
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (uint32_t e = 0; e < 7; ++e)
-      if (e < n) w[e >> 1] |= (uint32_t)(uint16_t)p[e] << (16 * (e & 1));
-    r = make_uint4(w[0], w[1], w[2], w[3]);
+    r.x = (uint32_t)(uint16_t)p[0];
   }
   return r;
 }
