@@ -17,9 +17,10 @@ namespace tsa {
 
 constexpr int kUnroll = 4;            // 16-byte loads in flight per lane
 // ... of the digit, histogram and moment passes.  int16 rows read at any element
-// boundary take two: with four the masked steps alone are 16 KB of code and
-// small boxes wait for it (95x91x97: histogram 10.9 -> 8.9 us; whole cubes lose a
-// sixth, 2^30 voxels 480 -> 545 us).
+// boundary take two: with four the masked steps are twice the code, which small
+// boxes wait for (27x25x23: histogram 9.1 -> 7.3 us; moments 37 to 39 -> 34 at
+// 395x397x393), though the histogram and the first digit of 1015x1013x503 voxels lose 4
+// and 7 % (320 -> 333 us, 196 -> 209).
 template <int DT, int VEC>
 constexpr int kUnrollOf = DT == 1 && VEC == 2 ? 2 : kUnroll;
 constexpr uint32_t kTileUnits = 8192; // vectors per rows tile (single-region calls), at most

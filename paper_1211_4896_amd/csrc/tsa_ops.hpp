@@ -493,10 +493,15 @@ struct HistAcc {
       : lds(l), lo(lo_), hi(hi_), scale(scale_), nbm1(nbins - 1), rshift(rshift_),
         rep(threadIdx.x & ((1u << rshift_) - 1u)), base(in_register(lds_byte_addr(l) + 4u * rep)),
         one(in_register(1u)) {}
-  TSA_DEV void vec(const uint4& r) {
+  TSA_DEV void vec(const uint4& r) { some(r, 0xFFu); }
+  template <int D = DT, class = std::enable_if_t<D == 1>>
+  TSA_DEV void masked(const uint4& r, uint32_t mask) {
+    some(r, mask);
+  }
+  TSA_DEV void some(const uint4& r, uint32_t mask) {  // mask: int16 only
     constexpr int N = Ty<DT>::EPV;
     float v[N];
-    bool in = true;
+    bool in = DT == 0 || mask == 0xFFu;
 #pragma unroll
     for (int e = 0; e < N; ++e) {
       v[e] = (float)Ty<DT>::get(r, e);
@@ -508,7 +513,7 @@ struct HistAcc {
         lds_add_at(((uint32_t)min((int32_t)((v[e] - lo) * scale), nbm1) << (rshift + 2u)) + base, one);
     } else {
 #pragma unroll
-      for (int e = 0; e < N; ++e) (*this)(v[e], true);
+      for (int e = 0; e < N; ++e) (*this)(v[e], DT == 0 || ((mask >> e) & 1u) != 0u);
     }
   }
   template <class T>
@@ -609,11 +614,16 @@ struct HistWinOutAcc {
   int32_t nbm1, w0;
   uint64_t* counts;
   uint32_t below = 0, above = 0;
-  TSA_DEV void vec(const uint4& r) {
+  TSA_DEV void vec(const uint4& r) { some(r, 0xFFu); }
+  template <int D = DT, class = std::enable_if_t<D == 1>>
+  TSA_DEV void masked(const uint4& r, uint32_t mask) {
+    some(r, mask);
+  }
+  TSA_DEV void some(const uint4& r, uint32_t mask) {  // mask: int16 only
     constexpr int N = Ty<DT>::EPV;
     float v[N];
     uint32_t rel[N];
-    bool in = true;
+    bool in = DT == 0 || mask == 0xFFu;
 #pragma unroll
     for (int e = 0; e < N; ++e) {
       v[e] = (float)Ty<DT>::get(r, e);
@@ -625,7 +635,7 @@ struct HistWinOutAcc {
       for (int e = 0; e < N; ++e) lds_inc(lds, rel[e]);
     } else {
 #pragma unroll
-      for (int e = 0; e < N; ++e) (*this)(v[e], true);
+      for (int e = 0; e < N; ++e) (*this)(v[e], DT == 0 || ((mask >> e) & 1u) != 0u);
     }
   }
   template <class T>

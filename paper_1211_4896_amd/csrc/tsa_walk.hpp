@@ -24,7 +24,8 @@
 //
 // Slots without a voxel (masked elements, lanes past the end) reach a float32
 // accumulator as NaN, which every one of them skips, with in_box true: no
-// per-element lane masks.  int16 slots carry in_box false.
+// per-element lane masks.  int16 slots carry in_box false, or a clear bit where the
+// accumulator takes a vector with a mask.
 #pragma once
 
 #include <type_traits>
@@ -90,6 +91,14 @@ TSA_DEV void visit_vecs(const uint4 (&r)[U], F& f) {
     for (int u = 0; u < U; ++u) visit_vec<DT>(r[u], f);
   }
 }
+
+// Whether F takes int16 vectors with a bit for each element that is a voxel: one copy
+// of its code then serves whole vectors, ends of rows and the end of the cube (three
+// copies: histogram of 30 K voxels 8.5 us against 7.0, of 2^30 401 against 351).
+template <class F, class = void>
+struct TakesMask : std::false_type {};
+template <class F>
+struct TakesMask<F, std::void_t<decltype(std::declval<F&>().masked(uint4{}, 0u))>> : std::true_type {};
 
 // What an empty slot holds.
 constexpr uint32_t kNaNBits = 0x7FC00000u;
@@ -162,6 +171,11 @@ TSA_DEV void visit_row_vec(uint4 r, uint32_t j, uint32_t vpr, uint32_t head_skip
       }
     }
     visit_vec<DT>(r, f);
+  } else if constexpr (TakesMask<F>::value) {
+    uint32_t mask = ok ? 0xFFu : 0u;
+    if (skips) mask &= 0xFFu << head_skip;
+    if (last) mask &= 0xFFu >> (8u - last_valid);
+    f.masked(r, mask);
   } else if (__ballot(!ok || (skips && head_skip != 0u) || (last && last_valid < (uint32_t)TT::EPV)) == 0ull) {
     visit_vec<DT>(r, f);
   } else {
@@ -267,8 +281,8 @@ TSA_DEV void walk_rows(const void* base, int64_t v_origin, int64_t v_ystride, in
 }
 
 // f(T value, bool in_box) is called once per element slot (see above for
-// slots without a voxel), or f.vec(uint4) once per whole vector where f has
-// it.  Every lane of the block calls f at the same points (never from
+// slots without a voxel), or f.vec(uint4), f.masked(uint4, bits) once per vector or
+// f.vecs once per chunk where f has them.  Every lane of the block calls f at the same points (never from
 // divergent code), so f may use wave-wide operations that need every lane.
 // f.chunk() is called by every thread of the block at the same points, after
 // at most blockDim.x * U vectors have been visited since the previous call,
@@ -301,7 +315,10 @@ TSA_DEV void walk(const Geom& g, F& f) {
         }
       };
       auto consume = [&](int64_t cb, const uint4(&r)[U]) {
-        if (DT == 0 || cb + chunk <= g.v1) {
+        if constexpr (TakesMask<F>::value) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) f.masked(r[u], cb + threadIdx.x + u * bs < g.v1 ? 0xFFu : 0u);
+        } else if (DT == 0 || cb + chunk <= g.v1) {
           visit_vecs<DT>(r, f);
         } else {
 #pragma unroll
