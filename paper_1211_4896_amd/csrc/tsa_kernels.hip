@@ -39,18 +39,22 @@ __global__ void k_fill_set(FillSet f) {
 // moments pass: one Partial per block
 // ---------------------------------------------------------------------------
 // float32 lanes sum about a shift of their own and the partials hold
-// (n, mean, M2); int16 partials hold exact integer sums.
-template <int DT, int VEC, bool NT>
+// (n, mean, M2); int16 partials hold exact integer sums.  float32 runs and tiles (ROWS)
+// are kernels of their own: see ShiftMomVecAcc.
+template <int DT, int VEC, bool NT, bool ROWS>
 __global__ __launch_bounds__(1024) void k_moments(Geom g, Partial* __restrict__ parts) {
+  using Acc = std::conditional_t<DT == 1, MomAcc<1>, std::conditional_t<ROWS, ShiftMomAcc, ShiftMomVecAcc>>;
   __shared__ MomShared sm;
-  if constexpr (DT == 0) {
-    ShiftMomAcc acc;
-    walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, acc);
-    block_store_centered(acc, sm, parts + blockIdx.x);
-  } else {
-    MomAcc<DT> acc;
+  Acc acc;
+  if constexpr (DT == 1) {
     walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, acc);
     block_store_partial(acc, sm, parts + blockIdx.x);
+  } else {
+    if constexpr (ROWS)
+      walk_tiles<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, acc);
+    else
+      walk_run<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, acc);
+    block_store_centered(acc, sm, parts + blockIdx.x);
   }
 }
 
@@ -1175,14 +1179,14 @@ struct Prep {
   int block, grid, bpc;
 };
 
-// Blocks per compute unit by call: the histogram and radix passes lose by a
-// third, the moments gain.  The fused trio takes three where rows are read one by
-// one (1711x1711x246 box: 561 + 617 us against 595 + 673), else two (1024x1024x1280
-// float32 voxels: 1.73 ms, with three 1.83; 400^3: 104 us, with three 112).
-constexpr int kBpcStats = 2, kBpcMoments = 3, kBpcHist = 2, kBpcSelect = 2;
+// Blocks per compute unit of a call's passes: two, and of the trio and the moments three
+// where rows are read one by one (two -> three: trio of a 1711x1711x246 box 595 + 673 ->
+// 561 + 617 us, moments of a 995x997x244 box 204 -> 186; of whole cubes 1.73 -> 1.83 ms
+// for the trio of 1024x1024x1280 float32 voxels, 169 -> 180 us for the moments of 640^3).
+constexpr int kBpc = 2, kBpcRows = 3;
 
 static int prepare(const tsa_cube* cube, const tsa_region* region, void* d_ws, size_t ws_bytes,
-                   tsa_stream_t stream, Prep* P, int bpc_default, int64_t cand_limit = INT64_MAX, bool trio = false) {
+                   tsa_stream_t stream, Prep* P, int rows_bpc = kBpc, int64_t cand_limit = INT64_MAX) {
   int st = check_cube(cube);
   if (st) return st;
   if ((st = region_box(cube, region, &P->box))) return st;
@@ -1194,8 +1198,7 @@ static int prepare(const tsa_cube* cube, const tsa_region* region, void* d_ws, s
   P->s = (hipStream_t)stream;
   const Tuning& T = tuning();
   P->block = T.block;
-  P->bpc = T.bpc ? T.bpc : bpc_default;
-  if (!T.bpc && trio && P->g.mode == 1) P->bpc = 3;
+  P->bpc = T.bpc ? T.bpc : P->g.mode == 1 ? rows_bpc : kBpc;
   int maxb = P->dev.cus * P->bpc;
   if (maxb > kMaxBlocks) maxb = kMaxBlocks;
   P->grid = pass_grid(P->g, P->vec, P->block, maxb);
@@ -1299,12 +1302,15 @@ int run_moments(const tsa_cube* cube, const tsa_region* region, tsa_result* d_ou
                 tsa_stream_t stream) {
   if (!d_out) return TSA_EINVAL;
   Prep P;
-  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcMoments);
+  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcRows);
   if (st) return st;
   Partial* parts = (Partial*)(P.ws + P.L.partials);
   TSA_TRACED("moments", P.s,
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 hipLaunchKernelGGL((k_moments<DT, VEC, NT>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, parts)));
+                 if (DT == 1 || P.g.mode == 0)
+                   hipLaunchKernelGGL((k_moments<DT, VEC, NT, false>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, parts);
+                 else
+                   hipLaunchKernelGGL((k_moments<DT, VEC, NT, DT == 0>), dim3(P.grid), dim3(P.block), 0, P.s, P.g, parts)));
   TSA_TRACED("moments_merge", P.s,
              hipLaunchKernelGGL(k_moments_merge, dim3(1), dim3(1024), 0, P.s, parts, P.grid, cube->dtype,
                                 (uint64_t)P.volume, d_out));
@@ -1325,7 +1331,7 @@ int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, floa
     scale = sc;
   }
   Prep P;
-  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcHist);
+  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P);
   if (st) return st;
   uint64_t* outl = d_outliers ? d_outliers : (uint64_t*)(P.ws + P.L.outl);
   const size_t budget = P.dev.lds_per_block < 65536 ? P.dev.lds_per_block : 65536;
@@ -1407,7 +1413,7 @@ int run_median(const tsa_cube* cube, const tsa_region* region, tsa_result* d_out
                tsa_stream_t stream) {
   if (!d_out) return TSA_EINVAL;
   Prep P;
-  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcSelect);
+  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P);
   if (st) return st;
   Count16Ask ask{};
   ask.out = d_out;
@@ -1469,7 +1475,7 @@ int run_histogram_chunked(const tsa_cube* cube, float lo, float hi, int32_t nbin
     scale = sc;
   }
   Prep P;
-  int st = prepare(cube, nullptr, d_ws, ws_bytes, stream, &P, kBpcHist);
+  int st = prepare(cube, nullptr, d_ws, ws_bytes, stream, &P);
   if (st) return st;
   std::vector<Slab> slabs;
   if ((st = slabs_of(cube, chunk_voxels, P, &slabs))) return st;
@@ -1497,7 +1503,7 @@ int run_median_chunked(const tsa_cube* cube, tsa_result* d_out, void* d_ws, size
                        int64_t chunk_voxels) {
   if (!d_out || chunk_voxels < 1) return TSA_EINVAL;
   Prep P;
-  int st = prepare(cube, nullptr, d_ws, ws_bytes, stream, &P, kBpcSelect);
+  int st = prepare(cube, nullptr, d_ws, ws_bytes, stream, &P);
   if (st) return st;
   std::vector<Slab> slabs;
   if ((st = slabs_of(cube, chunk_voxels, P, &slabs))) return st;
@@ -1666,7 +1672,7 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
   if (!d_out || !d_counts) return TSA_EINVAL;
   if (nbins < 1 || nbins > 65536) return TSA_EINVAL;
   Prep P;
-  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcStats, cand_limit, true);
+  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcRows, cand_limit);
   if (st) return st;
   const size_t budget = P.dev.lds_per_block < 65536 ? P.dev.lds_per_block : 65536;
   const size_t cand_small = (size_t)(P.block / kWave) * kWaveStage * 4;  // pass B's candidate staging
@@ -1754,7 +1760,7 @@ int run_quantile(const tsa_cube* cube, const tsa_region* region, double q, int32
                  void* d_ws, size_t ws_bytes, tsa_stream_t stream) {
   if (!d_out || !(q >= 0.0 && q <= 1.0) || digits < 1 || digits > 3) return TSA_EINVAL;
   Prep P;
-  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcSelect);
+  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P);
   if (st) return st;
   Count16Ask ask{};
   ask.qout = d_out;
@@ -1775,7 +1781,7 @@ int run_mad(const tsa_cube* cube, const tsa_region* region, double* d_out, void*
             tsa_stream_t stream) {
   if (!d_out) return TSA_EINVAL;
   Prep P;
-  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P, kBpcSelect);
+  int st = prepare(cube, region, d_ws, ws_bytes, stream, &P);
   if (st) return st;
   Count16Ask ask{};
   ask.qout = d_out;

@@ -287,100 +287,108 @@ TSA_DEV void walk_rows(const void* base, int64_t v_origin, int64_t v_ystride, in
 // f.chunk() is called by every thread of the block at the same points, after
 // at most blockDim.x * U vectors have been visited since the previous call,
 // so it may synchronise the block.
-// AHEAD: in the contiguous geometry the next chunk's loads are issued before
+// The contiguous geometry: AHEAD: the next chunk's loads are issued before
 // the present one is consumed, so a wave's processing never leaves it without
 // loads in flight (U more vectors of registers).
 template <int DT, int VEC, int U, bool NT, bool AHEAD = false, class F>
-TSA_DEV void walk(const Geom& g, F& f) {
+TSA_DEV void walk_run(const Geom& g, F& f) {
   using TT = Ty<DT>;
   using T = typename TT::T;
   const T* sb = (const T*)g.base;
   const int64_t bs = blockDim.x;
-  if (g.mode == 0) {
-    if constexpr (VEC != 0) {
-      const uint4* vb = (const uint4*)g.base;
-      const int64_t chunk = bs * U;
-      const int64_t stride = chunk * gridDim.x;
-      auto load = [&](int64_t cb, uint4(&r)[U]) {
-        const int64_t i = cb + threadIdx.x;
-        if (cb + chunk <= g.v1) {
+  if constexpr (VEC != 0) {
+    const uint4* vb = (const uint4*)g.base;
+    const int64_t chunk = bs * U;
+    const int64_t stride = chunk * gridDim.x;
+    auto load = [&](int64_t cb, uint4(&r)[U]) {
+      const int64_t i = cb + threadIdx.x;
+      if (cb + chunk <= g.v1) {
 #pragma unroll
-          for (int u = 0; u < U; ++u) r[u] = load16<NT>(vb + i + u * bs);
-        } else {  // the last, partial chunk of a block
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            r[u] = no_vec<DT>();
-            if (i + u * bs < g.v1) r[u] = load16<NT>(vb + i + u * bs);
-          }
-        }
-      };
-      auto consume = [&](int64_t cb, const uint4(&r)[U]) {
-        if constexpr (TakesMask<F>::value) {
-#pragma unroll
-          for (int u = 0; u < U; ++u) f.masked(r[u], cb + threadIdx.x + u * bs < g.v1 ? 0xFFu : 0u);
-        } else if (DT == 0 || cb + chunk <= g.v1) {
-          visit_vecs<DT>(r, f);
-        } else {
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int e = 0; e < TT::EPV; ++e) f(TT::get(r[u], e), cb + threadIdx.x + u * bs < g.v1);
-        }
-        f.chunk();
-      };
-      int64_t cb = g.v0 + (int64_t)blockIdx.x * chunk;
-      uint4 r[U];
-      if constexpr (AHEAD) {
-        if (cb < g.v1) {
-          load(cb, r);
-          for (;;) {
-            const int64_t nb = cb + stride;
-            uint4 n[U];
-            if (nb < g.v1) load(nb, n);
-            consume(cb, r);
-            if (nb >= g.v1) break;
-#pragma unroll
-            for (int u = 0; u < U; ++u) r[u] = n[u];
-            cb = nb;
-          }
-        }
-      } else {
-        for (; cb < g.v1; cb += stride) {
-          load(cb, r);
-          consume(cb, r);
-        }
-      }
-      // the elements outside the vectors: fewer than two vectors' worth
-      if (blockIdx.x == 0) {
-        const int64_t nh = g.h1 - g.h0, t = threadIdx.x, e = t < nh ? g.h0 + t : g.t0 + (t - nh);
-        const bool ok = e < (t < nh ? g.h1 : g.t1);
-        T v = no_elt<DT>();
-        if (ok) v = sb[e];
-        f(v, DT == 0 || ok);
-      }
-    } else {
-      const int64_t chunk = bs * U;
-      const int64_t stride = chunk * gridDim.x;
-      for (int64_t cb = g.v0 + (int64_t)blockIdx.x * chunk; cb < g.v1; cb += stride) {
+        for (int u = 0; u < U; ++u) r[u] = load16<NT>(vb + i + u * bs);
+      } else {  // the last, partial chunk of a block
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int64_t j = cb + u * bs + threadIdx.x;
-          const bool ok = j < g.v1;
-          T v = no_elt<DT>();
-          if (ok) v = sb[j];
-          f(v, DT == 0 || ok);
+          r[u] = no_vec<DT>();
+          if (i + u * bs < g.v1) r[u] = load16<NT>(vb + i + u * bs);
         }
-        f.chunk();
+      }
+    };
+    auto consume = [&](int64_t cb, const uint4(&r)[U]) {
+      if constexpr (TakesMask<F>::value) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) f.masked(r[u], cb + threadIdx.x + u * bs < g.v1 ? 0xFFu : 0u);
+      } else if (DT == 0 || cb + chunk <= g.v1) {
+        visit_vecs<DT>(r, f);
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < TT::EPV; ++e) f(TT::get(r[u], e), cb + threadIdx.x + u * bs < g.v1);
+      }
+      f.chunk();
+    };
+    int64_t cb = g.v0 + (int64_t)blockIdx.x * chunk;
+    uint4 r[U];
+    if constexpr (AHEAD) {
+      if (cb < g.v1) {
+        load(cb, r);
+        for (;;) {
+          const int64_t nb = cb + stride;
+          uint4 n[U];
+          if (nb < g.v1) load(nb, n);
+          consume(cb, r);
+          if (nb >= g.v1) break;
+#pragma unroll
+          for (int u = 0; u < U; ++u) r[u] = n[u];
+          cb = nb;
+        }
+      }
+    } else {
+      for (; cb < g.v1; cb += stride) {
+        load(cb, r);
+        consume(cb, r);
       }
     }
-    return;
+    // the elements outside the vectors: fewer than two vectors' worth
+    if (blockIdx.x == 0) {
+      const int64_t nh = g.h1 - g.h0, t = threadIdx.x, e = t < nh ? g.h0 + t : g.t0 + (t - nh);
+      const bool ok = e < (t < nh ? g.h1 : g.t1);
+      T v = no_elt<DT>();
+      if (ok) v = sb[e];
+      f(v, DT == 0 || ok);
+    }
+  } else {
+    const int64_t chunk = bs * U;
+    const int64_t stride = chunk * gridDim.x;
+    for (int64_t cb = g.v0 + (int64_t)blockIdx.x * chunk; cb < g.v1; cb += stride) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t j = cb + u * bs + threadIdx.x;
+        const bool ok = j < g.v1;
+        T v = no_elt<DT>();
+        if (ok) v = sb[j];
+        f(v, DT == 0 || ok);
+      }
+      f.chunk();
+    }
   }
-  // rows
+}
+// The tiles of a box.
+template <int DT, int VEC, int U, bool NT, class F>
+TSA_DEV void walk_tiles(const Geom& g, F& f) {
   for (uint32_t t = blockIdx.x; t < g.ntiles; t += gridDim.x) {
     const uint32_t r0 = t * g.rpt;
     walk_rows<DT, VEC, U, NT>(g.base, g.v_origin, g.v_ystride, g.v_zstride, g.ly, g.ly_m, g.vpr, g.vpr_m,
                               g.head_skip, g.last_valid, r0, min(g.rpt, g.nrows - r0), f);
   }
+}
+// Either, by the geometry.
+template <int DT, int VEC, int U, bool NT, bool AHEAD = false, class F>
+TSA_DEV void walk(const Geom& g, F& f) {
+  if (g.mode == 0)
+    walk_run<DT, VEC, U, NT, AHEAD>(g, f);
+  else
+    walk_tiles<DT, VEC, U, NT>(g, f);
 }
 
 }  // namespace tsa
