@@ -439,19 +439,12 @@ TSA_DEV void epilogue1(const BArgs& a, uint32_t q, BShared& sh, uint32_t* lds) {
       } else {
         s.prefix = d << kShift1;
         s.k = k - cum;
-        float lo = (float)bvalue_of_key(kmin, DT), hi = (float)bvalue_of_key(kmax, DT), scale = 0.f;
-        uint32_t ok = 0;
-        if (isfinite(lo) && isfinite(hi)) {
-          const float width = hi - lo;
-          if (isfinite(width)) {
-            scale = (float)a.nbins / width;
-            ok = (isfinite(scale) && scale != 0.0f) ? 1u : 0u;
-          }
-        }
+        float lo = (float)bvalue_of_key(kmin, DT), hi = (float)bvalue_of_key(kmax, DT), scale;
+        const bool ok = own_range(lo, hi, a.nbins, scale);
         s.lo = lo;
         s.hi = hi;
         s.scale = scale;
-        s.hist_ok = ok;
+        s.hist_ok = ok ? 1u : 0u;
         if (!ok) R.flags |= TSA_FLAG_HIST_SKIPPED;
         s.var_on = (DT == 0 && isfinite(mean) && one_pass_m2_at_risk(mean, R.m2 / (double)cnt)) ? 1u : 0u;
         s.shift = s.var_on ? (float)mean : 0.0f;
@@ -643,15 +636,8 @@ TSA_DEV void solo_box(const BArgs& a, uint32_t q, BShared& sh, CS& cs, uint32_t*
   // the histogram's range and scale, the shift of the second moment (every
   // thread computes the same values)
   const float lo = (float)vmin, hi = (float)vmax;
-  float scale = 0.f;
-  bool hist_on = false;
-  if (isfinite(lo) && isfinite(hi)) {
-    const float width = hi - lo;
-    if (isfinite(width)) {
-      scale = (float)a.nbins / width;
-      hist_on = isfinite(scale) && scale != 0.0f;
-    }
-  }
+  float scale;
+  const bool hist_on = own_range(lo, hi, a.nbins, scale);
   const double q2 = m2 < 0.0 ? 0.0 : m2;
   const bool var_on = DT == 0 && isfinite(mean) && one_pass_m2_at_risk(mean, q2 / (double)cnt);
   const float shift = var_on ? (float)mean : 0.0f;

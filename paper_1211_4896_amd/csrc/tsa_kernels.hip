@@ -605,17 +605,7 @@ TSA_DEV void mid_tail(const Partial* parts, int np, int dtype, uint64_t volume, 
     if (n > 0) {
       lo = (float)value_of_key(kmin, dtype);
       hi = (float)value_of_key(kmax, dtype);
-      if (isfinite(lo) && isfinite(hi)) {
-        if (lo == hi) {
-          ok = 1;
-        } else {
-          const float width = hi - lo;
-          if (isfinite(width)) {
-            scale = (float)nbins / width;
-            ok = (isfinite(scale) && scale != 0.0f) ? 1u : 0u;
-          }
-        }
-      }
+      ok = own_range(lo, hi, nbins, scale) ? 1u : 0u;
     }
     st->hist_ok = ok;
     st->lo = lo;

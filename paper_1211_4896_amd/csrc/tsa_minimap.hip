@@ -476,14 +476,8 @@ __global__ __launch_bounds__(kMMBlock) __attribute__((amdgpu_waves_per_eu(EPT <=
         R.std = sqrt(m2 / n);
         sh.go = 1;
         sh.k = (p.n - 1) / 2;
-        float scale = 0.f;
-        if (isfinite(lo) && isfinite(hi)) {
-          const float width = hi - lo;
-          if (isfinite(width)) {
-            scale = (float)a.nbins / width;
-            sh.hist_ok = (isfinite(scale) && scale != 0.0f) ? 1u : 0u;
-          }
-        }
+        float scale;
+        sh.hist_ok = own_range(lo, hi, a.nbins, scale) ? 1u : 0u;
         if (!sh.hist_ok) R.flags = TSA_FLAG_HIST_SKIPPED;
         sh.lo = lo;
         sh.scale = scale;

@@ -502,6 +502,16 @@ TSA_DEV void lds_flush(const uint32_t* lds, uint32_t nbins, uint32_t rshift, uin
   }
 }
 
+// Whether a histogram over the values' own extremes exists, and its scale (lo == hi,
+// which both zeros are too: 0, every value in bin 0).  An infinite extreme or width
+// makes the quotient 0 or NaN.
+TSA_DEV bool own_range(float lo, float hi, int32_t nbins, float& scale) {
+  const float s = (float)nbins / (hi - lo);
+  const bool ok = __builtin_isfinite(s) && s != 0.0f;
+  scale = ok ? s : 0.0f;
+  return ok || (lo == hi && __builtin_isfinite(lo));
+}
+
 // ---- histogram (Section 4.1) ---------------------------------------------------
 // LDS: (nbins << rshift) + kTrash words.  The vectors take the formula's minimum
 // value by value: it costs no time (1024x1024x1280 voxels with it 1723 us, without
