@@ -719,13 +719,12 @@ TSA_DEV void pass_b_tail(const Partial* parts2, SelState* st, const uint64_t* hi
 template <int DT, int VEC, bool NT>
 __global__ __launch_bounds__(1024) void k_pass_b(Geom g, int32_t nbins, uint32_t rshift, uint32_t stage,
                                                  SelState* __restrict__ st,
-                                                 uint64_t* __restrict__ counts, uint64_t* __restrict__ outl,
+                                                 uint64_t* __restrict__ counts,
                                                  uint64_t* __restrict__ hist2, uint32_t* __restrict__ cand,
                                                  Partial* __restrict__ parts2, Tail tl) {
   // dynamic LDS: [nbins << rshift] histogram, [kBins2] level-2 digits, then the
   // candidate staging of the block's waves
   extern __shared__ __align__(16) uint32_t lds[];
-  __shared__ uint32_t osm[32];
   __shared__ MomShared sm;
   __shared__ Partial sm_part;
   const uint32_t hsize = ((uint32_t)nbins << rshift) + kTrash;
@@ -790,62 +789,6 @@ __global__ __launch_bounds__(1024) void k_pass_bwin(Geom g, int32_t nbins, SelSt
     }
   }
   if (sel_on) lds_flush(l2, kBins2, 0, hist2);
-  if (var_on) {
-    block_store_var(b.var, sm, &sm_part);  // thread 0's
-    if (threadIdx.x == 0) publish_partial(sm_part, parts2 + blockIdx.x);
-  }
-  pass_b_tail(parts2, st, hist2, var_on, (double*)lds, tl);
-}
-
-// Pass B with 16-bit histogram counters (nbins too large for 32-bit LDS
-// counters): the histogram flushes its counters every `epoch` chunks.
-template <int DT>
-struct PassB16 {
-  Hist16Acc h;
-  Level2Acc<DT> l2;
-  VarAcc var;
-  bool hist_on, var_on;
-  template <class T>
-  TSA_DEV void operator()(T raw, bool in) {
-    if (hist_on) h(raw, in);
-    l2(raw, in);
-    if constexpr (DT == 0) {
-      if (var_on) var(raw, in);
-    }
-  }
-  TSA_DEV void chunk() {
-    if (hist_on) h.chunk();
-  }
-};
-
-template <int DT, int VEC, bool NT>
-__global__ __launch_bounds__(1024) void k_pass_b16(Geom g, int32_t nbins, uint32_t epoch, SelState* __restrict__ st,
-                                                   uint64_t* __restrict__ counts, uint64_t* __restrict__ outl,
-                                                   uint64_t* __restrict__ hist2, uint32_t* __restrict__ cand,
-                                                   Partial* __restrict__ parts2, Tail tl) {
-  extern __shared__ __align__(16) uint32_t lds[];  // [(nbins+1)/2] 16-bit counter pairs, then [kBins2] level-2 digits
-  __shared__ uint32_t osm[32];
-  __shared__ MomShared sm;
-  __shared__ Partial sm_part;
-  __shared__ CandShared cs;
-  const uint32_t hwords = ((uint32_t)nbins + 1u) >> 1;
-  uint32_t* l2 = lds + hwords;
-  const bool hist_on = st->hist_ok != 0;
-  const bool sel_on = st->done == 0;
-  const bool var_on = DT == 0 && st->var_on != 0;
-  if (!hist_on && !sel_on && !var_on) return;
-  lds_zero(lds, hwords + kBins2);
-  __syncthreads();
-  PassB16<DT> b{Hist16Acc{lds, st->lo, st->hi, st->scale, nbins - 1, 0, nbins, counts, epoch, 0u, true, 0u, 0u},
-                Level2Acc<DT>(l2, st->prefix, sel_on, st->compact != 0,
-                              cand_sink(cs, cand, &st->ncand, st->cand_cap)),
-                VarAcc{st->shift}, hist_on, var_on};
-  walk<DT, VEC, kUnrollOf<DT, VEC>, NT>(g, b);
-  b.l2.finish();
-  if (hist_on) b.h.flush();
-  __syncthreads();
-  if (sel_on) lds_flush(l2, kBins2, 0, hist2);
-  if (hist_on) block_add_outliers(b.h.below, b.h.above, outl, osm);
   if (var_on) {
     block_store_var(b.var, sm, &sm_part);  // thread 0's
     if (threadIdx.x == 0) publish_partial(sm_part, parts2 + blockIdx.x);
@@ -1252,19 +1195,6 @@ static void reset_select(const Prep& P, const SelState& init, uint64_t* d_counts
 }
 
 template <int DT, int VEC, bool NT>
-static int launch_pass_b16(const Prep& P, int block, int grid, size_t lds, int32_t nbins, uint32_t epoch,
-                           SelState* stp, uint64_t* d_counts, uint64_t* outl, uint64_t* h2, uint32_t* cand,
-                           Partial* parts2, const Tail& tl) {
-  if (lds > 65536 && hipFuncSetAttribute((const void*)k_pass_b16<DT, VEC, NT>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return TSA_EDEVICE;
-  TSA_TRACED("pass_b16", P.s,
-             hipLaunchKernelGGL((k_pass_b16<DT, VEC, NT>), dim3(grid), dim3(block), lds, P.s, P.g, nbins, epoch, stp,
-                                d_counts, outl, h2, cand, parts2, tl));
-  return TSA_OK;
-}
-
-template <int DT, int VEC, bool NT>
 static int launch_pass_bwin(const Prep& P, int block, int grid, size_t lds, int32_t nbins, SelState* stp,
                             uint64_t* d_counts, uint64_t* h2, uint32_t* cand, Partial* parts2, const Tail& tl) {
   if (hipFuncSetAttribute((const void*)k_pass_bwin<DT, VEC, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1667,9 +1597,10 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
   const size_t budget = P.dev.lds_per_block < 65536 ? P.dev.lds_per_block : 65536;
   const size_t cand_small = (size_t)(P.block / kWave) * kWaveStage * 4;  // pass B's candidate staging
   const bool wide = ((size_t)nbins + kTrash + kBins2) * 4 + cand_small > budget;
-  // 16-bit counters: (nbins+1)/2 words + level-2 digits, plus ~10 KB of static LDS
-  const size_t lds16 = ((((size_t)nbins + 1) / 2) + kBins2) * 4;
-  if (wide && lds16 + 10240 > P.dev.lds_per_block) return TSA_ENOTSUP;
+  // more bins: one 1024-lane block per compute unit, a window of 32-bit counters
+  const int win_block = 1024;
+  const size_t lds_win = ((size_t)kWinBins + kBins2 + (win_block / kWave) * kWaveStage) * 4;
+  if (wide && lds_win + sizeof(MomShared) + 1024 > P.dev.lds_per_block) return TSA_ENOTSUP;  // not on gfx950
   uint64_t* outl = d_outliers ? d_outliers : (uint64_t*)(P.ws + P.L.outl);
   Count16Ask ask{};
   ask.out = d_out;
@@ -1699,11 +1630,11 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
   Partial* parts2 = (Partial*)(P.ws + P.L.partials2);
   if (!wide) {
     // replicas only as far as bpc blocks of pass B still share a compute unit
-    // (its static LDS: candidate staging, moment reduction, outliers)
+    // (its static LDS: candidate staging, moment reduction)
     const size_t per_block = P.dev.lds_per_block / (size_t)P.bpc;
     // (and within the 64 KB a launch takes without raising its LDS limit)
     const size_t cap_b = per_block < budget ? per_block : budget;
-    auto fixed_of = [&](size_t cb) { return sizeof(MomShared) + 32 * 4 + cb + (kBins2 + kTrash) * 4 + 1024; };  // + slack
+    auto fixed_of = [&](size_t cb) { return sizeof(MomShared) + cb + (kBins2 + kTrash) * 4 + 1024; };  // + slack
     // the deep candidate stage when one replica of every bin still fits beside it
     uint32_t stage = kWaveStageBig;
     size_t cand_b = (size_t)(P.block / kWave) * stage * 4;
@@ -1718,30 +1649,14 @@ static int enqueue_stats(const tsa_cube* cube, const tsa_region* region, int32_t
     TSA_TRACED("pass_b", P.s,
       TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
                    hipLaunchKernelGGL((k_pass_b<DT, VEC, NT>), dim3(P.grid), dim3(P.block), ldsb, P.s, P.g, nbins,
-                                      rsb, stage, stp, hcopy, outl, h2, cand, parts2, tl)));
+                                      rsb, stage, stp, hcopy, h2, cand, parts2, tl)));
   } else {
-    // one 1024-thread block per compute unit: a window of 32-bit counters when
-    // the device grants the LDS, else 16-bit counters flushed in epochs
-    const int blk = 1024;
-    int grid = P.dev.cus;
-    if (grid > P.grid) grid = P.grid;
-    const size_t lds_win = ((size_t)kWinBins + kBins2 + (blk / kWave) * kWaveStage) * 4;
-    if (lds_win + sizeof(MomShared) + 1024 <= P.dev.lds_per_block) {
-      int stw = TSA_OK;
-      TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                   stw = (launch_pass_bwin<DT, VEC, NT>(P, blk, grid, lds_win, nbins, stp, d_counts, h2, cand,
-                                                        parts2, tl)));
-      if (stw) return stw;
-      return launch_last_digit(cube, P, tl, HistCopies{});
-    }
-    const int epv = P.vec ? (cube->dtype == TSA_F32 ? 4 : 8) : 1;
-    const int64_t ep = (65535 - 16) / ((int64_t)blk * kUnroll * epv);
-    if (ep < 1) return TSA_ENOTSUP;
-    int st2 = TSA_OK;
+    const int grid = P.grid < P.dev.cus ? P.grid : P.dev.cus;
+    int stw = TSA_OK;
     TSA_DISPATCH(cube->dtype, P.vec, tuning().nt,
-                 st2 = (launch_pass_b16<DT, VEC, NT>(P, blk, grid, lds16, nbins, (uint32_t)ep, stp, d_counts, outl,
-                                                     h2, cand, parts2, tl)));
-    if (st2) return st2;
+                 stw = (launch_pass_bwin<DT, VEC, NT>(P, win_block, grid, lds_win, nbins, stp, d_counts, h2, cand,
+                                                      parts2, tl)));
+    if (stw) return stw;
   }
   return launch_last_digit(cube, P, tl, wide ? HistCopies{} : HistCopies{hcopy, d_counts, nbins});
 }

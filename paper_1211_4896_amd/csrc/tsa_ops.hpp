@@ -767,58 +767,6 @@ TSA_DEV void block_add_outliers(uint32_t below, uint32_t above, uint64_t* g, uin
 }
 
 // ---- digit selection and moment merges (whole block / one thread) -----------
-// Block-wide choice of the digit holding rank k in a histogram of nb bins
-// (u32 counts).  Returns false when k is not inside the histogram.  SH provides
-// wsum[blockDim.x / 64], found, sel_digit, sel_cum and sel_bucket in LDS.
-template <class SH>
-TSA_DEV bool block_select_u32(const uint32_t* hist, int nb, uint64_t k, SH& sh, uint32_t* digit,
-                              uint64_t* cum_before, uint64_t* bucket) {
-  const int t = threadIdx.x, bs = blockDim.x;
-  const int per = (nb + bs - 1) / bs;
-  const int b0 = t * per;
-  uint64_t local = 0;
-  if (per <= 8) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {  // every read in flight at once
-      const uint32_t h = hist[min(b0 + i, nb - 1)];
-      local += (i < per && b0 + i < nb) ? h : 0u;
-    }
-  } else {
-    for (int i = 0; i < per; ++i)
-      if (b0 + i < nb) local += hist[b0 + i];
-  }
-  const int lane = t % kWave, w = t / kWave;
-  const uint64_t inc = wave_scan_incl_u64(local);
-  if (lane == kWave - 1) sh.wsum[w] = inc;
-  if (t == 0) sh.found = 0;
-  __syncthreads();
-  uint64_t base = inc - local;
-  for (int i = 0; i < w; ++i) base += sh.wsum[i];
-  if (local > 0 && k >= base && k < base + local) {
-    uint64_t cum = base;
-    int d = b0;
-    for (int i = 0; i < per; ++i) {
-      const uint64_t h = (b0 + i < nb) ? hist[b0 + i] : 0;
-      if (k < cum + h) {
-        d = b0 + i;
-        break;
-      }
-      cum += h;
-    }
-    sh.sel_digit = (uint32_t)d;
-    sh.sel_cum = cum;
-    sh.sel_bucket = hist[d];
-    sh.found = 1;
-  }
-  __syncthreads();
-  const bool found = sh.found != 0;
-  *digit = sh.sel_digit;
-  *cum_before = sh.sel_cum;
-  *bucket = sh.sel_bucket;
-  __syncthreads();
-  return found;
-}
-
 // Wave-wide inclusive prefix sum of 32-bit values: Hillis-Steele steps of 1,
 // 2, 4 and 8 lanes inside each row of 16 (DPP row shifts; a lane with no
 // source adds 0), then lane 15 of rows 0 and 2 added to rows 1 and 3, then
@@ -833,10 +781,10 @@ TSA_DEV uint32_t wave_scan_incl_u32(uint32_t v) {
   return v;
 }
 
-// block_select_u32 for histograms whose total fits in 32 bits (a mini-map
-// cell): 32-bit DPP scans instead of 64-bit shuffles, and every wave total
-// read at once.  SH provides wsum32[16] (16-byte aligned), found, sel_digit, sel_cum32 and
-// sel_bucket32 in LDS; blockDim.x is at most 1024.
+// Block-wide choice of the digit holding rank k in a histogram of nb bins whose total
+// fits in 32 bits: DPP scans, and every wave total read at once.  Returns false when k
+// is not inside the histogram.  SH provides wsum32[16] (16-byte aligned), found,
+// sel_digit, sel_cum32 and sel_bucket32 in LDS; blockDim.x is at most 1024.
 // at(i): where counter i lies.
 struct InOrder {
   TSA_DEV uint32_t operator()(uint32_t i) const { return i; }
@@ -1116,12 +1064,6 @@ TSA_DEV void cand_append_slow(bool m, uint32_t key, uint64_t bal, CandSink<PUBLI
   const uint32_t off = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
   if (m) k.buf[w * k.stage + k.fill + off] = key;
   k.fill += n;
-}
-
-template <bool PUBLISH>
-TSA_DEV void cand_append(bool m, uint32_t key, CandSink<PUBLISH>& k) {
-  const uint64_t bal = __ballot(m);
-  if (bal != 0) cand_append_slow(m, key, bal, k);
 }
 
 // Whole block (blockDim.x at most 1024): every wave's still-staged keys
