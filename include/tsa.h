@@ -220,8 +220,8 @@ int tsa_quantile(const tsa_cube* cube, const tsa_region* region, double q, int32
  * the non-NaN values, x - m rounded to single precision (int16: exact).  A
  * value equal to m deviates by +0, also when m is infinite (where the IEEE
  * difference would be NaN), so the rank is taken over all count values.
- * Two passes over large float32 regions, one over large int16 regions, four or
- * five over small ones.  d_out (device, 3 doubles) = (m, MAD, count); NaN, NaN,
+ * Two passes over float32 regions of 2^27 to 2.6e10 voxels, one over int16 regions
+ * from 2^23 voxels on, four or five over others.  d_out (device, 3 doubles) = (m, MAD, count); NaN, NaN,
  * 0 without a valid voxel.
  */
 int tsa_mad(const tsa_cube* cube, const tsa_region* region, double* d_out, void* d_ws, size_t ws_bytes,

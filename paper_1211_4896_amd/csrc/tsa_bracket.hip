@@ -29,6 +29,8 @@ constexpr double kSigmas = 4.0, kRanks = 12.0;  // the bounds' distance from the
 //   2^26: median 103 -> 131, 220 -> 116, 579 -> 126; 0.9-quantile 147 -> 123; MAD 254 -> 254
 //   2^27: median 178 -> 172, 401 -> 155, 1132 -> 165; 0.9-quantile 259 -> 166; MAD 439 -> 336
 //   2^28: median 335 -> 255, 774 -> 236, 2233 -> 245; 0.9-quantile 493 -> 248; MAD 829 -> 504
+// A region without a valid voxel pays for the launches (median of 2^27 voxels 93 ->
+// 131): its first digit would have ended the call.
 constexpr int64_t kBracketMin = 1ll << 27;
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;  // a sampled NaN (no value has this key)
 constexpr uint32_t kKeyMinusInf = 0x007FFFFFu, kKeyPlusInf = 0xFF800000u;
@@ -315,7 +317,7 @@ TSA_DEV void finish(SelState* st, uint32_t key, uint64_t n, const BracketAsk& as
 // Bound by HBM: 1024x1024x1280 voxels (5.4 GB) 0.91 ms, 5.9 TB/s (deviations
 // 0.96), two blocks per compute unit.  One block 1.13, three 0.98, loads a
 // chunk ahead 0.94 and 1.12 for the deviations.  MAD and 0.9-quantile of those
-// voxels: 6.45 -> 3.05 ms.
+// voxels: 6.55 -> 2.95 ms.
 template <int VEC, bool NT, bool DEV>
 __global__ __launch_bounds__(1024) void k_bracket(Geom g, uint32_t depth, BracketMem* m, uint32_t* __restrict__ list, uint32_t cap,
                                                   uint64_t* __restrict__ parts, SelState* __restrict__ st,
@@ -466,7 +468,9 @@ static_assert(8 * (kBins1 + kBins2 + kBins3) % 16 == 0 &&
 size_t bracket_bytes() { return (sizeof(BracketMem) + 255) / 256 * 256; }
 
 // Voxels to sample for a region of `volume` voxels whose list may hold cand_cap
-// keys (the sample's own keys lie behind it); 0: by key digits.
+// keys (the sample's own keys lie behind it); 0: by key digits.  With the 2^26 keys
+// of the largest workspaces: 2^18 voxels up to 7.0e9, 2^20 up to 1.40e10, 2^22
+// up to 2.676e10 (107 GB), above that none.
 uint32_t bracket_samples(int64_t volume, uint32_t cand_cap) {
   if (volume < kBracketMin) return 0;
   for (uint32_t ns = kSampleBlocks * kSampleThreads; ns <= 1u << 22; ns *= 4) {

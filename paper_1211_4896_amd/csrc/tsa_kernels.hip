@@ -1270,7 +1270,7 @@ int run_histogram(const tsa_cube* cube, const tsa_region* region, float lo, floa
     return launch_ok();
   }
   // a window of 32-bit counters where a sample of the region puts most values,
-  // one 1024-lane block per compute unit; else 16-bit counters in epochs
+  // one 1024-lane block per compute unit; else (not on gfx950) 16-bit counters in epochs
   const size_t lds_win = (size_t)kWinBins * 4;
   if (lds_win + 1024 <= P.dev.lds_per_block) {
     int32_t* w0p = (int32_t*)(P.ws + P.L.state + offsetof(SelState, win0));

@@ -113,9 +113,9 @@ struct MomAcc<0, COUNT> {
     }
   }
   // None of them NaN.  Four values are summed before they meet the running
-  // sums: a quarter of the roundings at the sums' size (two blocks per compute
-  // unit, 1024x1024x1280 voxels: error of the mean and M2 2.5e-15 -> 0.7e-15 of
-  // the exact ones, time 1.73 -> 1.735 ms).
+  // sums: a quarter of the roundings at the sums' size (1024x1024x1280 voxels,
+  // two blocks per compute unit: error of the mean and M2 2.5e-15 -> 0.4e-15, with
+  // three blocks one by one 1.5e-15; time 1.73 -> 1.735 ms).
   TSA_DEV void four(const Four& f) {
     const double v[4] = {(double)f.v[0], (double)f.v[1], (double)f.v[2], (double)f.v[3]};
     s += (v[0] + v[1]) + (v[2] + v[3]);
