@@ -41,6 +41,7 @@ def _traced(call):
 
 @pytest.mark.parametrize("times,bracketed", [(112, True), (300, True), (400, False)])
 def test_repeated_slab(times, bracketed):
+    torch.cuda.empty_cache()  # blocks that earlier cases left in torch's cache
     nbytes = 4 * times * int(np.prod(SHAPE))
     if torch.cuda.mem_get_info()[0] < nbytes + (4 << 30):
         pytest.skip(f"needs {nbytes >> 30} GiB of free device memory")
@@ -62,3 +63,5 @@ def test_repeated_slab(times, bracketed):
         assert tsa.quantile(dev, q) == (float(v[k // times]), 0.0, n * times), q
     dev_sorted = np.sort(np.abs(v - v[(n - 1) // 2]))
     assert tsa.mad(dev) == (float(v[(n - 1) // 2]), float(dev_sorted[(n - 1) // 2]), n * times)
+    del dev
+    torch.cuda.empty_cache()
