@@ -30,7 +30,7 @@ def _check_all(host, boxes, tune, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "i16"])
-@pytest.mark.parametrize("nq", [1, 2, 1024, 1025])
+@pytest.mark.parametrize("nq", [1, 2, 255, 256, 257, 512, 513, 1025])
 @pytest.mark.parametrize("tune", [None, (1024, 256, 4, 65536)])
 def test_every_histogram(dtype, nq, tune):
     print("case batch set-up histograms", dtype, nq, tune, flush=True)
