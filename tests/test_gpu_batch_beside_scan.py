@@ -27,28 +27,28 @@ def test_batch_does_not_wait_for_the_scan():
     counts = torch.zeros(256, dtype=torch.int64, device="cuda:0")
     res = torch.zeros(72, dtype=torch.uint8, device="cuda:0")
     hists = torch.zeros(64, dtype=torch.int64, device="cuda:0")
-    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    s1 = torch.cuda.Stream()
+    others = [torch.cuda.Stream() for _ in range(3)]  # some stream may share the scan's hardware queue
 
     def scan():
         assert api.tsa_histogram(ctypes.byref(cb), None, -1000.0, 1000.0, 256, counts.data_ptr(), None, wb.data_ptr(),
                                  wb.numel(), s1.cuda_stream) == 0
 
-    def batch():
+    def batch(s2):
         assert api.tsa_region_batch(ctypes.byref(cs), boxes.data_ptr(), 1, 64, res.data_ptr(), hists.data_ptr(), None,
                                     ws.data_ptr(), ws.numel(), s2.cuda_stream) == 0
 
-    for _ in range(4):  # code loaded, graphs captured
-        scan()
-        batch()
-        torch.cuda.synchronize()
-    shares = []
-    for _ in range(7):
+    def share(s2):
         begin, scanned, batched = (torch.cuda.Event(enable_timing=True) for _ in range(3))
         begin.record(s1)
         scan()
         scanned.record(s1)
-        batch()
+        batch(s2)
         batched.record(s2)
         torch.cuda.synchronize()
-        shares.append(begin.elapsed_time(batched) / begin.elapsed_time(scanned))
-    assert sorted(shares)[3] < 0.7, shares  # one that waits for the scan ends after it
+        return begin.elapsed_time(batched) / begin.elapsed_time(scanned)
+
+    for s2 in others * 2:  # code loaded, graphs captured
+        share(s2)
+    shares = [sorted(share(s2) for _ in range(5))[2] for s2 in others]
+    assert min(shares) < 0.7, shares  # a batch that waits for the scan ends with it or after it
